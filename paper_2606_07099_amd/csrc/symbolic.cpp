@@ -288,21 +288,42 @@ int analyze(int32_t n_bus, const int32_t* bus_type, const int32_t* y_indptr,
   std::vector<std::vector<int32_t>> adj(nb);
   for (int32_t c = 0; c < nb; ++c)
     for (int32_t j : nbr[comp_bus[c]]) if (j != S.slack) adj[c].push_back(comp[j]);
-  // ---- exact minimum degree on the elimination graph (Tinney scheme 2)
+  // ---- minimum degree on the elimination graph (Tinney scheme 2), weighed
+  // against the depth of the elimination tree: next comes the bus of lowest
+  // 4 * degree + depth (ties: lowest degree, then lowest bus), depth = longest
+  // chain of eliminated buses below it.  By degree alone the upper rows string into chains of
+  // one-row levels, and every level is a barrier-separated pass of each
+  // factorisation and solve.  A quarter of a degree per level keeps the fill
+  // (118-, 300-, 1354-, 9241-bus grids: 667, 1771, 8431, 52438 blocks against
+  // 665, 1797, 8357, 52698) at 15, 18, 34, 62 levels against 29, 27, 62, 81;
+  // half a degree saves no more than three further levels and costs 2 % fill.
   std::vector<int32_t> order; order.reserve(nb);
   std::vector<std::vector<int32_t>> later(nb);
-  std::vector<char> done(nb, 0);
-  std::vector<int32_t> tmp;
-  for (int32_t step = 0; step < nb; ++step) {
-    int32_t v = -1;
-    size_t best = SIZE_MAX;
-    for (int32_t c = 0; c < nb; ++c)
-      if (!done[c] && adj[c].size() < best) { best = adj[c].size(); v = c; }
+  std::vector<int32_t> tmp, depth(nb, 0);
+  auto score_of = [&](int32_t c) {
+    const int64_t deg = (int64_t)adj[c].size();
+    return ((4 * deg + depth[c]) << 32) + deg;
+  };
+  // a heap of (score, bus) whose entries go stale when a bus's score changes
+  using Entry = std::pair<int64_t, int32_t>;
+  std::priority_queue<Entry, std::vector<Entry>, std::greater<Entry>> heap;
+  std::vector<int64_t> score(nb);
+  for (int32_t c = 0; c < nb; ++c) heap.push({score[c] = score_of(c), c});
+  while (!heap.empty()) {
+    const Entry top = heap.top();
+    heap.pop();
+    const int32_t v = top.second;
+    if (score[v] != top.first) continue;
+    score[v] = -1;
     order.push_back(v);
-    done[v] = 1;
     later[v] = adj[v];
     const std::vector<int32_t>& cl = later[v];
-    for (int32_t u : cl) merge_into(adj[u], cl, v, u, tmp);
+    for (int32_t u : cl) {
+      merge_into(adj[u], cl, v, u, tmp);
+      depth[u] = std::max(depth[u], depth[v] + 1);
+      const int64_t now = score_of(u);
+      if (now != score[u]) heap.push({score[u] = now, u});
+    }
     adj[v].clear();
   }
   // ---- renumber by (elimination-tree level, elimination position): a

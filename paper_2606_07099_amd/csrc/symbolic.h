@@ -4,8 +4,9 @@
 // by the Y_bus pattern and the bus-type partition (symbolic-analysis and
 // BDE-layout passages of Sec. III-B).  This module builds, once per network:
 //
-//  * a fill-reducing elimination order of the non-slack buses (exact minimum
-//    degree on the bus graph, ties to the lowest bus index);
+//  * a fill-reducing elimination order of the non-slack buses (minimum degree
+//    on the bus graph, weighed against the depth of the elimination tree,
+//    ties to the lowest bus index);
 //  * the 2x2-block pattern of L+U: every non-slack bus i owns the block
 //    unknowns (theta_i, |V|_i) and the block equations (dP_i, dQ_i); on a PV
 //    bus the |V| unknown and the dQ row are padding (identity diagonal, zero
