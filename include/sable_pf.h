@@ -305,12 +305,13 @@ int pf_operator_pattern(int32_t n_bus, const int32_t* bus_type, const int32_t* y
  * in the order of pf_operator_pattern's CSR, evaluated in FP64 (Algorithm 1's
  * entry formulas; selectors are 1).  count may exceed the template's batch:
  * only the template's pattern is used, not its workspace.  The operator
- * tables are built with the template; the first call allocates a buffer of
- * 32 * count * n_bus bytes for the per-bus voltages and injections (device
- * memory, released by pf_template_destroy); a later call with a larger count
- * grows that buffer (after a device synchronisation), any other call
- * allocates nothing.  Calls on one template share the buffer: calls that
- * overlap on different streams race.  Asynchronous on hip_stream.
+ * tables are built with the template.  Networks of up to 4096 buses keep the
+ * per-bus voltages and currents on chip and the call allocates nothing.  For
+ * larger ones the first call allocates a buffer of 32 * count * n_bus bytes
+ * for them (device memory, released by pf_template_destroy); a later call
+ * with a larger count grows that buffer (after a device synchronisation), any
+ * other call allocates nothing; calls on one template share the buffer, and
+ * calls that overlap on different streams race.  Asynchronous on hip_stream.
  * Errors: PF_EINVAL, PF_ENOMEM, PF_EHIP.
  */
 int pf_operator_values(pf_template* tpl, int32_t which, int32_t count, const double* vm,
@@ -320,11 +321,12 @@ int pf_operator_values(pf_template* tpl, int32_t which, int32_t count, const dou
  * pf_operator_values for callers that cannot allocate device memory (code
  * under HIP graph capture, serving loops, harnesses that forbid hipMalloc):
  * the same arguments, values and errors, but the per-bus voltages and
- * injections live in a fixed 32 MiB device array that the library holds on
- * each device it runs on until the process ends, so the call allocates
- * nothing, not even on its first use.  A batch whose state (32 bytes per bus
- * and scenario) exceeds the array is processed in consecutive pieces on
- * hip_stream; a network of more than 2^20 buses is rejected with PF_EINVAL.
+ * injections of networks above 4096 buses live in a fixed 32 MiB device array
+ * that the library holds on each device it runs on until the process ends, so
+ * the call allocates nothing, not even on its first use.  A batch whose state
+ * there (32 bytes per bus and scenario) exceeds the array is processed in
+ * consecutive pieces on hip_stream; a network of more than 2^20 buses is
+ * rejected with PF_EINVAL.
  * All calls on one device share the array: calls that overlap on one device
  * (different streams or threads) race.  Asynchronous on hip_stream.
  * Errors: PF_EINVAL, PF_EHIP.

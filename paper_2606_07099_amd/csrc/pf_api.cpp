@@ -46,11 +46,10 @@ struct pf_template {
   void* wsl_t = nullptr;
   size_t ws_bytes = 0;
   bool have_factors = false;
-  // operator export tables, built with the template: the base entries
-  // (int4 each), then per operator its source map, CSR row pointers and
-  // column indices (one scenario's pattern)
+  // operator export tables, built with the template: per operator the base
+  // entry of every value (int4 each), CSR row pointers and column indices
+  // (one scenario's pattern)
   void* d_ops = nullptr;
-  int32_t op_nbase = 0;
   int32_t op_off[sable::OP_COUNT] = {};
   int32_t op_nnz[sable::OP_COUNT] = {};
   int32_t op_ip_off[sable::OP_COUNT] = {};
@@ -238,13 +237,15 @@ int build_operator_tables(pf_template* t) {
   const int rc = sable::build_operators(S.n_bus, S.bus_type.data(), S.y_rp.data(), S.y_ci.data(), ops, err);
   if (rc != PF_OK) return fail(rc, "operator tables: " + err);
   std::vector<int32_t> buf;
-  for (const sable::BaseEntry& e : ops.base) buf.insert(buf.end(), {e.kind, e.i, e.j, e.q});
-  t->op_nbase = (int32_t)ops.base.size();
   for (int k = 0; k < sable::OP_COUNT; ++k) {
     const sable::OperatorPattern& op = ops.op[k];
+    buf.resize((buf.size() + 3) / 4 * 4);   // records start 16-byte aligned
     t->op_off[k] = (int32_t)buf.size();
     t->op_nnz[k] = (int32_t)op.src.size();
-    buf.insert(buf.end(), op.src.begin(), op.src.end());
+    for (int32_t s : op.src) {
+      const sable::BaseEntry& e = ops.base[s];
+      buf.insert(buf.end(), {e.kind, e.i, e.j, e.q});
+    }
     t->op_ip_off[k] = (int32_t)buf.size();
     buf.insert(buf.end(), op.indptr.begin(), op.indptr.end());
     t->op_ix_off[k] = (int32_t)buf.size();
@@ -304,8 +305,7 @@ int operator_params(pf_template* t, int which, int count, const double* vm, cons
   if (count > 0 && (!vm || !va || !values)) return fail(PF_EINVAL, nm + ": NULL array");
   const unsigned char* img = static_cast<const unsigned char*>(t->d_sym);
   p = OpParams{};
-  p.base = static_cast<const int4*>(t->d_ops);
-  p.src = static_cast<const int*>(t->d_ops) + t->op_off[which];
+  p.rec = reinterpret_cast<const int4*>(static_cast<const int*>(t->d_ops) + t->op_off[which]);
   p.y_rp = reinterpret_cast<const int*>(img + t->so.y_rp);
   p.y_ci = reinterpret_cast<const int*>(img + t->so.y_ci);
   p.y_g = reinterpret_cast<const double*>(img + t->so.y_g);
@@ -598,6 +598,7 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
   he = hipMemset(t->ws_i, 0xff, bi);
   if (he == hipSuccess && std::max(t->lds_bytes, t->adj_lds) > 64 * 1024)
     he = sable::set_lds_limits(std::max(t->lds_bytes, t->adj_lds));
+  if (he == hipSuccess) he = sable::set_operator_lds(S.n_bus);
   if (he == hipSuccess) he = hipDeviceSynchronize();
   if (he != hipSuccess) { pf_template_destroy(t); return hip_fail(he, "pf_template_build: set-up"); }
   t->ws_bytes = pk.buf.size() + bd + bt + bi + bsl;
@@ -775,7 +776,7 @@ int pf_operator_values(pf_template* t, int32_t which, int32_t count, const doubl
   int rc = sable::operator_params(t, which, count, vm, va, values, "pf_operator_values", p, dev);
   if (rc != PF_OK) return rc;
   DeviceGuard g(dev);
-  if ((size_t)count > t->opef_count) {   // grow the state buffer (previous work may still read it)
+  if (!sable::operator_state_in_lds(p.n_bus) && (size_t)count > t->opef_count) {   // grow the state buffer (previous work may still read it)
     (void)hipDeviceSynchronize();
     if (t->d_opef) (void)hipFree(t->d_opef);
     t->d_opef = nullptr;

@@ -10,9 +10,9 @@
 #include "pf_operators.h"
 #include "sable_pf.h"
 
-// Operator refresh without allocation: the per-bus state (e, f, P, Q) that
-// the value kernel reads lives in a fixed device array instead of the
-// template's growable buffer.  Each device holds its own copy of the array
+// Operator refresh without allocation.  Networks whose per-bus state the value
+// kernel holds in LDS need no scratch at all.  For larger ones the state (e, f,
+// P, Q) lives in a fixed device array instead of the template's growable buffer.  Each device holds its own copy of the array
 // until the process ends; host code reaches it only through the address
 // hipGetSymbolAddress returns for the current device, taken once per device
 // on the first call there.  Batches whose state does not fit are processed
@@ -70,7 +70,8 @@ extern "C" int pf_operator_values_static(pf_template* t, int32_t which, int32_t 
   hipError_t he = hipSuccess;
   void* ptr = scratch_on(dev, he);
   if (ptr) {
-    const int piece = (int)std::min<size_t>((size_t)count, kStaticStateDoubles / per);
+    const size_t fit = sable::operator_state_in_lds(p.n_bus) ? (size_t)count : kStaticStateDoubles / per;
+    const int piece = (int)std::min<size_t>((size_t)count, fit);
     for (int b0 = 0; b0 < count && he == hipSuccess; b0 += piece) {
       sable::OpParams q = p;
       q.count = std::min(piece, count - b0);

@@ -12,18 +12,22 @@
 namespace sable {
 
 struct OpParams {
-  const int4* base;      // [nnz_base] {kind, i, j, q} (BaseKind, bus pair, Y_bus position)
-  const int* src;        // [nnz] base entry of each value of the operator
+  const int4* rec;       // [nnz] the base entry {kind, i, j, q} of each value (BaseKind, bus pair, Y_bus position)
   const int *y_rp, *y_ci;
   const double *y_g, *y_b;
   const double *vm, *va; // [count][n_bus] state of each scenario
   double* ef;            // [count][n_bus] (e, f, P, Q): e + jf = V, P + jQ = V conj(I), formed first
+                         // (networks whose state does not fit in LDS only, else unused)
   double* values;        // [count][nnz]: the value array of the batch-global (block-diagonal) CSR
   int nnz, n_bus, count;
 };
 
-// two launches on st: the per-bus state, then the values
+// one launch on st, or two where the per-bus state goes through p.ef
 hipError_t launch_operator_values(const OpParams& p, hipStream_t st);
+// whether a network's per-bus state fits in LDS (p.ef is then not needed)
+bool operator_state_in_lds(int n_bus);
+// raises the kernels' LDS limit on the current device where the network needs it
+hipError_t set_operator_lds(int n_bus);
 
 // the batch-global CSR of the block-diagonal embedding of one scenario's
 // pattern (indptr[rows + 1], indices[nnz], device) for `count` scenarios:

@@ -1,11 +1,11 @@
 // Value refresh of the Jacobian operators (Algorithm 1 for the entry values,
 // the block-aware indexing of Algorithm 2 for their placement), fused: one
-// thread per (scenario, value of the operator) reads the base entry that
-// feeds the value, evaluates it at the scenario's state and writes it in
-// the operator's value order, so the writes are coalesced for transposed
-// operators too and no base value buffer is materialised.  A first launch
-// forms, once per (scenario, bus), the rectangular voltage e + jf and the
-// calculated injection P + jQ that the diagonal entries need.
+// thread per (scenario, value of the operator) evaluates the base entry that
+// feeds the value at the scenario's state and writes it in the operator's
+// value order, so the writes are coalesced for transposed operators too and
+// no base value buffer is materialised.  The per-bus state that the entries
+// read (voltage and calculated current) is formed once per workgroup in LDS;
+// networks too large for that form it in device memory in a launch of its own.
 #include "pf_operators.h"
 
 #include <algorithm>
@@ -87,8 +87,7 @@ __global__ void __launch_bounds__(256) k_operator_values(OpParams p) {
   if (o >= groups * p.nnz) return;
   const size_t g = o / p.nnz;
   const int v = (int)(o - g * p.nnz);
-  const int t = p.src[v];
-  const int4 be = p.base[t];
+  const int4 be = p.rec[v];
   const int kind = be.x, i = be.y, j = be.z, q = be.w;
   const double G = (kind != BK_SEL && q >= 0) ? p.y_g[q] : 0.0;
   const double Bv = (kind != BK_SEL && q >= 0) ? p.y_b[q] : 0.0;
@@ -97,9 +96,139 @@ __global__ void __launch_bounds__(256) k_operator_values(OpParams p) {
     p.values[b * p.nnz + v] = kind == BK_SEL ? 1.0 : entry_value(p, kind, i, j, G, Bv, b);
 }
 
+// The same with the state in LDS.  A workgroup owns SC scenarios and one of
+// `splits` runs of the operator's values: it forms cos, sin, |V| of every bus
+// and the current I = Y V there, then evaluates its values from LDS alone, so
+// that the random gathers of a bus pair cost LDS cycles instead of cache
+// lines.  With u = (cos theta, sin theta) the entries need no division:
+// V_j / |V_j| = u_j and S_i / |V_i| = u_i conj(I_i).
+// Bound: the write of the values (8 bytes each), behind 32 bytes of pattern
+// per value (record and Y_bus entry) from L2, shared by the SC scenarios.
+// J1, J1^T, J2^T and J3^T of 1024 scenarios of the 1354-bus grid (308 MB of
+// values, 65 us at the rate of a large copy): 493 us with the state in device
+// memory (two launches per operator), 201 us here with two scenarios per
+// workgroup, about 235 us with one.
+constexpr int kOpBusDoubles = 5;   // (cos, sin), (I_re, I_im), |V|
+
+template <int SC, int NT>
+__global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
+  // the sums below are written with their fused operations, so that a value
+  // does not depend on how many scenarios share its workgroup
+#pragma clang fp contract(off)
+  extern __shared__ __align__(16) double op_smem[];
+  const int n = p.n_bus, tid = threadIdx.x;
+  double2* u = reinterpret_cast<double2*>(op_smem);        // [n][SC]
+  double2* cur = u + (size_t)n * SC;                       // [n][SC]
+  double* mag = reinterpret_cast<double*>(cur + (size_t)n * SC);
+  const int group = blockIdx.x / splits, split = blockIdx.x - group * splits;
+  const int b0 = group * SC;
+  for (int q = tid; q < n * SC; q += NT) {
+    const int s = q / n, i = q - s * n;
+    double sn = 0.0, cs = 1.0, v = 1.0;
+    if (b0 + s < p.count) {
+      const size_t o = (size_t)(b0 + s) * n + i;
+      sincos(p.va[o], &sn, &cs);
+      v = p.vm[o];
+    }
+    u[i * SC + s] = make_double2(cs, sn);
+    mag[i * SC + s] = v;
+  }
+  __syncthreads();
+  for (int i = tid; i < n; i += NT) {
+    double ir[SC], ii[SC];
+#pragma unroll
+    for (int s = 0; s < SC; ++s) ir[s] = ii[s] = 0.0;
+    for (int k = p.y_rp[i]; k < p.y_rp[i + 1]; ++k) {
+      const int j = p.y_ci[k];
+      const double g = p.y_g[k], b = p.y_b[k];
+#pragma unroll
+      for (int s = 0; s < SC; ++s) {
+        const double2 w = u[j * SC + s];
+        const double v = mag[j * SC + s], e = v * w.x, f = v * w.y;
+        ir[s] = fma(-b, f, fma(g, e, ir[s]));
+        ii[s] = fma(b, e, fma(g, f, ii[s]));
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < SC; ++s) cur[i * SC + s] = make_double2(ir[s], ii[s]);
+  }
+  __syncthreads();
+  const int per = (p.nnz + splits - 1) / splits;
+  const int v1 = min(p.nnz, (split + 1) * per);
+  for (int v = split * per + tid; v < v1; v += NT) {
+    const int4 r = p.rec[v];
+    const int kind = r.x, i = r.y, j = r.z;
+    const bool sel = kind == BK_SEL, y = !sel && r.w >= 0;
+    const double G = y ? p.y_g[r.w] : 0.0, B = y ? p.y_b[r.w] : 0.0;
+    const bool dva = kind == BK_DP_DVA || kind == BK_DQ_DVA;
+    // dP/dtheta and dQ/d|V| share one form, dQ/dtheta and dP/d|V| the other
+    const bool first = kind == BK_DP_DVA || kind == BK_DQ_DVM;
+#pragma unroll
+    for (int s = 0; s < SC; ++s) {
+      if (b0 + s >= p.count) break;
+      const double2 wi = u[i * SC + s];
+      const double vi = mag[i * SC + s];
+      double x;
+      if (i != j) {
+        const double2 wj = u[j * SC + s];
+        const double cc = fma(wi.x, wj.x, wi.y * wj.y), ss = fma(wi.y, wj.x, -(wi.x * wj.y));
+        const double w = dva ? vi * mag[j * SC + s] : vi;
+        const double t = first ? fma(B, cc, -(G * ss)) : fma(G, cc, B * ss);
+        x = w * (kind == BK_DP_DVM ? -t : t);
+      } else {
+        const double2 I = cur[i * SC + s];
+        const double a = fma(wi.x, I.x, wi.y * I.y);       // P / |V|
+        const double q = fma(wi.y, I.x, -(wi.x * I.y));    // Q / |V|
+        if (dva) x = vi * (first ? fma(B, vi, q) : fma(G, vi, -a));
+        else x = first ? fma(B, vi, -q) : -fma(G, vi, a);
+      }
+      p.values[(size_t)(b0 + s) * p.nnz + v] = sel ? 1.0 : x;
+    }
+  }
+}
+
+constexpr size_t kOpLdsLimit = 160 * 1024;
+
+bool operator_state_in_lds(int n_bus) {
+  return (size_t)n_bus * kOpBusDoubles * sizeof(double) <= kOpLdsLimit;
+}
+
+hipError_t set_operator_lds(int n_bus) {
+  if (2 * (size_t)n_bus * kOpBusDoubles * sizeof(double) <= 64 * 1024) return hipSuccess;   // the default limit
+  hipError_t e = hipSuccess;
+  for (const void* f : {reinterpret_cast<const void*>(&k_operator_lds<1, 512>),
+                        reinterpret_cast<const void*>(&k_operator_lds<2, 512>),
+                        reinterpret_cast<const void*>(&k_operator_lds<1, 1024>),
+                        reinterpret_cast<const void*>(&k_operator_lds<2, 1024>)}) {
+    const hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOpLdsLimit);
+    if (r != hipSuccess) e = r;
+  }
+  return e;
+}
+
 hipError_t launch_operator_values(const OpParams& p, hipStream_t st) {
   const size_t nst = (size_t)p.count * p.n_bus, total = (size_t)p.count * p.nnz;
   if (total == 0) return hipSuccess;
+  if (operator_state_in_lds(p.n_bus)) {
+    // two scenarios per workgroup where that still leaves one per compute
+    // unit; 1024 threads per workgroup from 512 buses on (118 buses x4096:
+    // 67 us with 512, 84 with 1024; 1354 buses x1024: 234 and 177, on one set
+    // of buffers), and the
+    // values of few scenarios split over as many workgroups as there are
+    // compute units
+    constexpr int kCus = 256;
+    const size_t bus = kOpBusDoubles * sizeof(double) * (size_t)p.n_bus;
+    const int sc = p.count >= 2 * kCus && 2 * bus <= kOpLdsLimit ? 2 : 1;
+    const int nt = p.n_bus >= 512 ? 1024 : 512;
+    const int groups = (p.count + sc - 1) / sc;
+    const int splits = std::max(1, std::min((p.nnz + nt - 1) / nt, kCus / groups));
+    const dim3 g((unsigned)((size_t)groups * splits)), b(nt);
+    if (sc == 1 && nt == 512) hipLaunchKernelGGL((k_operator_lds<1, 512>), g, b, bus, st, p, splits);
+    else if (sc == 2 && nt == 512) hipLaunchKernelGGL((k_operator_lds<2, 512>), g, b, 2 * bus, st, p, splits);
+    else if (sc == 1) hipLaunchKernelGGL((k_operator_lds<1, 1024>), g, b, bus, st, p, splits);
+    else hipLaunchKernelGGL((k_operator_lds<2, 1024>), g, b, 2 * bus, st, p, splits);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_operator_state, dim3((unsigned)((nst + 255) / 256)), dim3(256), 0, st, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
