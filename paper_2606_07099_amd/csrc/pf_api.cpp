@@ -25,6 +25,7 @@ struct pf_template {
   bool fp32 = false;
   int nt = 256;
   bool lds_res = false;
+  bool rows = false;         // HBM-resident slices factor row by row
   size_t lds_bytes = 0;
   int gmin = 4;
   int wstride = 0;
@@ -100,7 +101,8 @@ int round_up(int v, int m) { return (v + m - 1) / m * m; }
 // gk: how the eight gathered values e f |V| 1/|V| I_re I_im dV_re dV_im of a
 // bus are grouped: 8 all together, 2 in the pairs (e, f), (|V|, 1/|V|),
 // (I_re, I_im), (dV_re, dV_im) that the passes read together, 1 one array each
-sable::StateLayout make_layout(int n_bus, int nb, int nnzb, int gk) {
+// dinv_in_place: the inverted pivot blocks take their blocks' place
+sable::StateLayout make_layout(int n_bus, int nb, int nnzb, int gk, bool dinv_in_place) {
   sable::StateLayout L{};
   const int nbr = round_up(n_bus, 4), v2 = round_up(2 * nb, 4);
   int o = 0;
@@ -115,7 +117,11 @@ sable::StateLayout make_layout(int n_bus, int nb, int nnzb, int gk) {
   int t = 0;
   L.o_y = t; t += round_up(2 * nb, 8);
   L.o_lu = t; t += round_up(4 * nnzb, 8);
-  L.o_dinv = t; t += round_up(4 * nb, 8);
+  if (dinv_in_place) {
+    L.o_dinv = L.o_lu;
+  } else {
+    L.o_dinv = t; t += round_up(4 * nb, 8);
+  }
   L.st = t;
   return L;
 }
@@ -284,7 +290,7 @@ int adjoint_impl(const char* name, pf_template* t, const double* g_vm, const dou
   const int aw = t->adj_slice < 0 ? -t->adj_slice : t->adj_slice;
   const int agrid = aw ? (t->batch + aw - 1) / aw : t->batch;
   hipError_t he = sable::launch_adjoint(kp, t->fp32, t->adj_slice, agrid, aw ? t->adj_nt : t->nt, t->adj_lds,
-                                        static_cast<hipStream_t>(hip_stream));
+                                        t->rows, static_cast<hipStream_t>(hip_stream));
   if (he != hipSuccess) return hip_fail(he, (nm + ": launch").c_str());
   return PF_OK;
 }
@@ -424,117 +430,124 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
     if (S.bus_type[i] != PF_BUS_SLACK) ord_p[i] = np++;
     if (S.bus_type[i] == PF_BUS_PQ) ord_q[i] = nq++;
   }
-  Packer pk;
   sable::SymOffsets& so = t->so;
-  // level metadata in chunks of whole rows: read in place from the LDS image
-  // by LDS-resident slices, staged chunk by chunk in LDS by HBM-resident ones
-  sable::LevelChunks chunks;
-  // HBM-resident slices of S scenarios: S as large as keeps at least one
-  // slice per compute unit and leaves room in LDS for the tail copy (its
-  // tail-column blocks, pivot inverses and right-hand sides) and at least
-  // 2048 words of staged metadata; the chunk budget takes what remains.
-  // S = 1 always fits: the tail holds at most 32 x 32 blocks.
-  const int n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-  // the LDS copy of the tail: per scenario its tail-column blocks (stride
-  // odd, so that the scenarios' copies start in different banks), pivot
-  // inverses and right-hand sides, then the tail program's solve prefix
-  const size_t tail_nbs = S.tail_cblk.size() | 1;
-  auto tail_bytes = [&](int sl) {
-    return (size_t)sl * tsz * (4 * tail_nbs + 6 * (size_t)S.tail_t) + 4 * (size_t)S.tail_prog_prefix;
-  };
-  int hbm_slice = 1;
-  while (hbm_slice < sable::kMaxSlice && batch / (2 * hbm_slice) >= n_cu) hbm_slice *= 2;
-  while (hbm_slice > 1 && sable::kScratchBytes + tail_bytes(hbm_slice) + 4 * 2048 > max_lds) hbm_slice /= 2;
-  if (sable::kScratchBytes + tail_bytes(hbm_slice) + 4 * 2048 > max_lds) {
-    delete t;
-    return fail(PF_EINVAL, "pf_template_build: the dense tail does not fit in LDS");
-  }
-  // the slice's right-hand side / solution vector y of the triangular
-  // solves lives in LDS too when that leaves the full metadata budget
-  const size_t y_bytes = ((size_t)2 * S.nb * hbm_slice * tsz + 15) / 16 * 16;
-  size_t room = (max_lds - sable::kScratchBytes - tail_bytes(hbm_slice)) / 4;
-  const bool y_in_lds = room >= y_bytes / 4 + kChunkInts;
-  if (y_in_lds) room -= y_bytes / 4;
-  const int32_t budget = (int32_t)std::min<size_t>(kChunkInts, room / 4 * 4);
-  rc = sable::build_level_chunks(S, budget, chunks, err);
-  if (rc != 0) { delete t; return fail(PF_EINVAL, err); }
-  so.bus_type = (int)pk.add(S.bus_type); so.bus_blk = (int)pk.add(S.bus_blk);
-  so.y_rp = (int)pk.add(S.y_rp); so.y_ci = (int)pk.add(S.y_ci);
-  so.y_g = (int)pk.add(S.y_g); so.y_b = (int)pk.add(S.y_b);
-  so.rp = (int)pk.add(S.rp); so.ci = (int)pk.add(S.ci); so.diag = (int)pk.add(S.diag);
-  so.fill4 = (int)pk.add(S.fill4);
-  so.tail_pos = (int)pk.add(S.tail_pos); so.tail_split = (int)pk.add(S.tail_split);
-  so.tail_mask = (int)pk.add(S.tail_mask);
-  so.f_ptr = (int)pk.add(chunks.f_ptr); so.f_blob = (int)pk.add(chunks.f_blob);
-  so.fs_ptr = (int)pk.add(chunks.fs_ptr); so.fs_blob = (int)pk.add(chunks.fs_blob);
-  so.bs_ptr = (int)pk.add(chunks.bs_ptr); so.bs_blob = (int)pk.add(chunks.bs_blob);
-  so.newton_bytes = (int)pk.align();
-  so.ut_ptr = (int)pk.add(chunks.ut_ptr); so.ut_blob = (int)pk.add(chunks.ut_blob);
-  so.lt_ptr = (int)pk.add(chunks.lt_ptr); so.lt_blob = (int)pk.add(chunks.lt_blob);
-  so.tt_ptr = (int)pk.add(chunks.tt_ptr); so.tt_pairs = (int)pk.add(chunks.tt_pairs);
-  so.y_tr = (int)pk.add(S.y_tr);
-  so.adj_bytes = (int)pk.align();
-  so.tail_cblk = (int)pk.add(S.tail_cblk);
-  so.tail_prog = (int)pk.add(S.tail_prog);
-  so.ord_p = (int)pk.add(ord_p); so.ord_q = (int)pk.add(ord_q);
-  so.total_bytes = (int)pk.align();
   sable::Dims& dm = t->dims;
   dm.n_bus = S.n_bus; dm.nb = S.nb; dm.nnzb = S.nnzb(); dm.nj = S.nb + S.n_pq; dm.npq = S.n_pq;
   dm.npvpq = S.nb; dm.nlev_l = S.n_levels_l(); dm.nlev_u = S.n_levels_u();
   dm.nlev_f = S.n_task_levels; dm.nlev_fs = S.n_fs_levels;
   dm.nlev_bs = (int)S.lev_um_ptr.size() - 1;
   dm.tail_t = S.tail_t; dm.tail_base = S.tail_base;
-  dm.nch_f = (int)chunks.f_ptr.size() - 1;
-  dm.nch_fs = (int)chunks.fs_ptr.size() - 1;
-  dm.nch_bs = (int)chunks.bs_ptr.size() - 1;
-  // the LDS copy of the tail reads its elimination program from the
-  // metadata area (free while the tail is factored) when the area, grown
-  // within the room left, holds it
+  // the LDS copy of the tail: per scenario its tail-column blocks (stride
+  // odd, so that the scenarios' copies start in different banks), pivot
+  // inverses and right-hand sides; the tail program's solve prefix
+  const size_t tail_nbs = S.tail_cblk.size() | 1;
   dm.tail_nbs = (int)tail_nbs;
+  dm.tail_nblk = (int)S.tail_cblk.size();
   dm.tail_prog_ints = (int)S.tail_prog.size();
   dm.tail_prog_prefix = S.tail_prog_prefix;
   const size_t upd_words = S.tail_prog.size() - (size_t)S.tail_prog_prefix;
-  dm.tail_prog_lds = upd_words <= room ? 1 : 0;
-  dm.chunk_ints = std::max<int>(chunks.max_ints, dm.tail_prog_lds ? (int)(upd_words + 3) / 4 * 4 : 0);
-  dm.tail_nblk = (int)S.tail_cblk.size();
-  dm.nch_ut = (int)chunks.ut_ptr.size() - 1;
-  dm.nch_lt = (int)chunks.lt_ptr.size() - 1;
+  const size_t prefix_bytes = (4 * (size_t)S.tail_prog_prefix + 15) / 16 * 16;
+  auto tail_bytes = [&](int sl) { return (size_t)sl * tsz * (4 * tail_nbs + 6 * (size_t)S.tail_t); };
 
-  // ---- launch shape: LDS-resident slices of S <= 4 scenarios (256 threads,
+  // packs the device image for one storage of the blocks
+  auto pack = [&](const sable::LuStorage& st, const sable::LevelChunks& chunks, const sable::RowChunks* rows) {
+    Packer pk;
+    so.bus_type = (int)pk.add(S.bus_type); so.bus_blk = (int)pk.add(S.bus_blk);
+    so.y_rp = (int)pk.add(S.y_rp); so.y_ci = (int)pk.add(S.y_ci);
+    so.y_g = (int)pk.add(S.y_g); so.y_b = (int)pk.add(S.y_b);
+    // the row starts (of the L parts), columns and tail positions in storage order
+    std::vector<int32_t> rp(S.rp), ci(S.nnzb()), split(S.tail_split), cblk(S.tail_cblk), prog(S.tail_prog);
+    for (int32_t p = 0; p < S.nnzb(); ++p) ci[st.pos[p]] = S.ci[p];
+    if (st.split) {
+      for (int32_t a = 0; a < S.nb; ++a) rp[a] = st.pos[S.rp[a]];
+      for (int32_t l = 0; l < S.tail_t; ++l)
+        split[l] = rp[S.tail_base + l] + S.tail_split[l] - S.rp[S.tail_base + l];
+    }
+    for (int32_t& p : cblk) p = st.pos[p];
+    for (int32_t k = 0; k < S.tail_t; ++k) prog[8 * k + 7] = st.dinv[S.tail_base + k];
+    so.rp = (int)pk.add(rp); so.ci = (int)pk.add(ci); so.diag = (int)pk.add(S.diag);
+    so.fill4 = rows ? 0 : (int)pk.add(S.fill4);
+    so.tail_pos = (int)pk.add(S.tail_pos); so.tail_split = (int)pk.add(split);
+    so.tail_mask = (int)pk.add(S.tail_mask);
+    so.f_ptr = (int)pk.add(chunks.f_ptr); so.f_blob = (int)pk.add(chunks.f_blob);
+    so.fs_ptr = (int)pk.add(chunks.fs_ptr); so.fs_blob = (int)pk.add(chunks.fs_blob);
+    so.bs_ptr = (int)pk.add(chunks.bs_ptr); so.bs_blob = (int)pk.add(chunks.bs_blob);
+    so.newton_bytes = (int)pk.align();
+    so.ut_ptr = (int)pk.add(chunks.ut_ptr); so.ut_blob = (int)pk.add(chunks.ut_blob);
+    so.lt_ptr = (int)pk.add(chunks.lt_ptr); so.lt_blob = (int)pk.add(chunks.lt_blob);
+    so.tt_ptr = (int)pk.add(chunks.tt_ptr); so.tt_pairs = (int)pk.add(chunks.tt_pairs);
+    so.y_tr = (int)pk.add(S.y_tr);
+    so.adj_bytes = (int)pk.align();
+    so.tail_cblk = (int)pk.add(cblk);
+    so.tail_prog = (int)pk.add(prog);
+    so.ord_p = (int)pk.add(ord_p); so.ord_q = (int)pk.add(ord_q);
+    so.lu_pos = (int)pk.add(st.pos);
+    so.r_ptr = so.r_blob = so.fill_col = so.fill_gb = 0;
+    if (rows) {
+      std::vector<int32_t> col(S.nnzb());
+      std::vector<double> gb(2 * (size_t)S.nnzb(), 0.0);
+      for (int32_t p = 0; p < S.nnzb(); ++p) {
+        const int32_t bus = S.blk_bus[S.ci[p]], y = S.lu_src[p], at = st.pos[p];
+        col[at] = bus | (y < 0 ? sable::kFillNone : 0) | (S.bus_type[bus] == PF_BUS_PV ? sable::kFillPv : 0);
+        if (y >= 0) { gb[2 * (size_t)at] = S.y_g[y]; gb[2 * (size_t)at + 1] = S.y_b[y]; }
+      }
+      so.r_ptr = (int)pk.add(rows->ptr); so.r_blob = (int)pk.add(rows->blob);
+      so.fill_col = (int)pk.add(col); so.fill_gb = (int)pk.add(gb);
+    }
+    so.total_bytes = (int)pk.align();
+    dm.nch_f = (int)chunks.f_ptr.size() - 1;
+    dm.nch_fs = (int)chunks.fs_ptr.size() - 1;
+    dm.nch_bs = (int)chunks.bs_ptr.size() - 1;
+    dm.nch_ut = (int)chunks.ut_ptr.size() - 1;
+    dm.nch_lt = (int)chunks.lt_ptr.size() - 1;
+    dm.nch_r = rows ? (int)rows->ptr.size() - 1 : 0;
+    return pk;
+  };
+
+  // ---- launch shape: LDS-resident slices of S <= 4 scenarios (512 threads,
   // one wavefront per scenario's register-resident tail) when they fit,
   // choosing S to maximise the scenarios resident per CU; HBM-resident
   // slices of up to 16 scenarios otherwise
-  t->lay = make_layout(S.n_bus, S.nb, S.nnzb(), 1);
+  Packer pk;
+  t->lay = make_layout(S.n_bus, S.nb, S.nnzb(), 1, false);
   t->llay = make_lds_layout(S.n_bus, S.nb, S.nnzb(), t->fp32);
   const size_t lds_cu = std::max<size_t>(max_lds, (size_t)prop.maxSharedMemoryPerMultiProcessor);
   const size_t per_scen = 8 * (size_t)t->llay.sd + tsz * (size_t)t->llay.st;
   int best_s = 0;
   size_t best_score = 0;
   const int res_nt = sable::res_newton_threads(t->fp32);
-  const bool res_ok = opt.block_threads == 0 || opt.block_threads == res_nt;
-  for (int sl : {4, 2, 1}) {
-    if (!res_ok || sl > sable::kResMaxSlice) continue;
-    const size_t need = sable::kScratchBytes + (size_t)so.newton_bytes + sl * per_scen;
-    if (need > max_lds) continue;
-    const size_t score = (lds_cu / need) * sl;
-    if (score > best_score) { best_score = score; best_s = sl; }
-  }
   int nt = opt.block_threads;
   t->wstride = 0;
   t->gmin = 4;
-  // the adjoint: LDS-resident slices (256 threads, the tail in registers)
-  // whenever the Newton slices are, as wide as fits
   t->alay = make_adj_layout(S.n_bus, S.nb, S.nnzb());
   const size_t per_adj = 8 * (size_t)t->alay.sd + tsz * (size_t)t->alay.st;
   t->adj_slice = 0;
-  if (best_s > 0) {
-    for (int sl : {4, 2, 1}) {
-      const size_t need = sable::kScratchBytes + (size_t)so.adj_bytes + sl * per_adj;
-      if (need <= max_lds) { t->adj_slice = sl; t->adj_nt = sable::kResThreads; t->adj_lds = need; break; }
+  if ((opt.block_threads == 0 || opt.block_threads == res_nt) && sable::kScratchBytes + per_scen < max_lds) {
+    // level metadata read in place from the LDS image
+    sable::LevelChunks chunks;
+    const sable::LuStorage st = sable::storage_by_position(S);
+    if (sable::build_level_chunks(S, kChunkInts, chunks, err, &st) == 0) {
+      pk = pack(st, chunks, nullptr);
+      for (int sl : {4, 2, 1}) {
+        if (sl > sable::kResMaxSlice) continue;
+        const size_t need = sable::kScratchBytes + (size_t)so.newton_bytes + sl * per_scen;
+        if (need > max_lds) continue;
+        const size_t score = (lds_cu / need) * sl;
+        if (score > best_score) { best_score = score; best_s = sl; }
+      }
+      // the adjoint: LDS-resident slices (the tail in registers) whenever the
+      // Newton slices are, as wide as fits
+      if (best_s > 0) {
+        for (int sl : {4, 2, 1}) {
+          const size_t need = sable::kScratchBytes + (size_t)so.adj_bytes + sl * per_adj;
+          if (need <= max_lds) { t->adj_slice = sl; t->adj_nt = sable::kResThreads; t->adj_lds = need; break; }
+        }
+        // no LDS-resident adjoint slice fits: both run HBM-resident, where the
+        // adjoint reads the forward solve's slice workspace in place
+        if (t->adj_slice == 0) best_s = 0;
+      }
+      dm.chunk_ints = chunks.max_ints;
     }
-    // no LDS-resident adjoint slice fits: both run HBM-resident, where the
-    // adjoint reads the forward solve's slice workspace in place
-    if (t->adj_slice == 0) best_s = 0;
   }
   if (best_s > 0) {
     t->lds_res = true;
@@ -542,18 +555,75 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
     t->lds_bytes = sable::kScratchBytes + (size_t)so.newton_bytes + best_s * per_scen;
     nt = res_nt;
   } else {
-    // HBM-resident: S scenarios interleaved per slice, S as large as keeps
-    // at least one slice per compute unit
+    // HBM-resident: S scenarios interleaved per slice, S as large as keeps at
+    // least one slice per compute unit and leaves room in LDS for the tail
+    // copy and for staged metadata; S = 1 always fits: the tail holds at most
+    // 32 x 32 blocks.  The rows of the row-by-row factorisation have to fit
+    // beside the metadata too (in the place of the tail copy, which is made
+    // after it); a network with a row too long for that even with S = 1
+    // (thousands of neighbours) factors by levels in place.
     t->lds_res = false;
-    const int sl = hbm_slice;
+    // a full workgroup of 16 wavefronts: measured fastest for every slice
+    // width (more lanes per level of the elimination schedule)
+    if (nt == 0) nt = 1024;
+    const int n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+    int sl = 1;
+    while (sl < sable::kMaxSlice && batch / (2 * sl) >= n_cu) sl *= 2;
+    sable::LevelChunks chunks;
+    sable::RowChunks rows;
+    const size_t fixed = sable::kScratchBytes + prefix_bytes;
+    size_t y_bytes = 0, area = 0;
+    int32_t budget = 0;
+    auto plan = [&](bool by_rows) -> int {
+      // what the metadata can have beside the tail copy (S > 1: at most half
+      // of it where rows need buffers) and, when that leaves the full metadata
+      // budget, beside the slice's right-hand side / solution vector y: every
+      // solve's gathers then stay on chip
+      if (fixed + tail_bytes(sl) + 4 * 2048 > max_lds) { err = "pf_template_build: the dense tail does not fit in LDS"; return PF_EINVAL; }
+      size_t room = max_lds - fixed - tail_bytes(sl);
+      y_bytes = ((size_t)2 * S.nb * sl * tsz + 15) / 16 * 16;
+      const int32_t want = by_rows && sl > 1 ? kChunkInts / 2 : kChunkInts;
+      if (room >= y_bytes + 4 * (size_t)want) room -= y_bytes;
+      else y_bytes = 0;
+      budget = (int32_t)std::min<size_t>(want, room / 16 * 4);
+      const sable::LuStorage st = by_rows ? sable::storage_split(S) : sable::storage_by_position(S);
+      int r = sable::build_level_chunks(S, budget, chunks, err, &st);
+      if (r != 0) return r;
+      // the tail's update words are staged in the metadata area (free while
+      // the tail is factored) when the area, grown within the room, holds them
+      dm.tail_prog_lds = (upd_words + 3) / 4 * 16 <= room ? 1 : 0;
+      dm.chunk_ints = std::max<int>(chunks.max_ints, dm.tail_prog_lds ? (int)(upd_words + 3) / 4 * 4 : 0);
+      if (by_rows) {
+        dm.chunk_ints = std::max(dm.chunk_ints, budget);
+        area = max_lds - fixed - y_bytes - 4 * (size_t)dm.chunk_ints;
+        r = sable::build_row_chunks(S, st, sl, nt, (int64_t)(area / (4 * tsz * sl)), budget, rows, err);
+        if (r != 0) return r;
+      } else {
+        area = tail_bytes(sl);
+      }
+      pk = pack(st, chunks, by_rows ? &rows : nullptr);
+      return 0;
+    };
+    // Slices of one scenario factor by levels: there the chain of a row's
+    // steps, not the traffic, sets the time (1354-bus grid, 37 scenarios, FP64
+    // layer: 1.04 ms by levels, 1.25 by rows; 9241-bus grid, mixed: 9.4 and
+    // 10.1 ms), while 16 scenarios per slice gain 1.1 to 1.5 times.
+    t->rows = true;
+    while ((rc = sl > 1 ? plan(true) : PF_EINVAL) != 0 && sl > 1) sl /= 2;
+    if (rc != 0) {
+      t->rows = false;
+      sl = 1;
+      rc = plan(false);
+    }
+    if (rc != 0) { delete t; return fail(PF_EINVAL, err); }
     t->slice = sl;
     // grouped per-bus values: a slice of several scenarios reads a bus's
     // values of all of them at once, a slice of one reads them in pairs
-    t->lay = make_layout(S.n_bus, S.nb, S.nnzb(), sl > 1 ? 8 : 2);
-    t->lds_bytes = sable::kScratchBytes + 4 * (size_t)dm.chunk_ints + tail_bytes(sl);
-    t->lds_bytes = (t->lds_bytes + 15) / 16 * 16;
+    t->lay = make_layout(S.n_bus, S.nb, S.nnzb(), sl > 1 ? 8 : 2, t->rows);
+    dm.tail_off = (int)(fixed + 4 * (size_t)dm.chunk_ints);
+    t->lds_bytes = (dm.tail_off + area + 15) / 16 * 16;
     dm.y_lds_off = 0;
-    if (y_in_lds) {
+    if (y_bytes) {
       dm.y_lds_off = (int)t->lds_bytes;
       t->lds_bytes += y_bytes;
     }
@@ -561,9 +631,6 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
     t->adj_slice = -sl;
     t->adj_nt = 1024;   // as the Newton kernel: more lanes per level of the transposed solves
     t->adj_lds = t->lds_bytes;
-    // a full workgroup of 16 wavefronts: measured fastest for every slice
-    // width (more lanes per level of the elimination schedule)
-    if (nt == 0) nt = 1024;
   }
   t->nt = nt;
 
@@ -656,7 +723,7 @@ int pf_solve_batch(pf_template* t, const double* pd, const double* qd, const dou
   kp.iters_out = iters; kp.status_out = status; kp.fnorm_out = final_mismatch;
   const int grid = (t->batch + t->slice - 1) / t->slice;
   hipError_t he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res,
-                                       static_cast<hipStream_t>(hip_stream));
+                                       t->rows, static_cast<hipStream_t>(hip_stream));
   if (he != hipSuccess) return hip_fail(he, "pf_solve_batch: launch");
   t->have_factors = t->opt.keep_factors != 0;
   return PF_OK;
@@ -710,27 +777,27 @@ int pf_eval_batch(pf_template* t, int32_t mode, int32_t count, const double* pd,
   switch (mode) {
     case PF_EVAL_MISMATCH:
       kp.mode = sable::MODE_EVAL_MISMATCH;
-      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, st);
+      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->rows, st);
       break;
     case PF_EVAL_STEP:
       kp.mode = sable::MODE_EVAL_STEP;
-      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, st);
+      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->rows, st);
       break;
     case PF_EVAL_JACOBIAN:
       he = sable::launch_jacobian_dense(kp, count, st);
       break;
     case PF_EVAL_FILL:
       kp.mode = sable::MODE_EVAL_FILL;
-      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, st);
+      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->rows, st);
       break;
     case PF_EVAL_ADJOINT:
       kp.mode = sable::MODE_EVAL_FACTOR;
-      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, st);
+      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->rows, st);
       if (he == hipSuccess) {
         kp.mode = sable::MODE_EVAL_ADJOINT;
         const int aw = t->adj_slice < 0 ? -t->adj_slice : t->adj_slice;
         he = sable::launch_adjoint(kp, t->fp32, t->adj_slice, aw ? (count + aw - 1) / aw : count,
-                                   aw ? t->adj_nt : t->nt, t->adj_lds, st);
+                                   aw ? t->adj_nt : t->nt, t->adj_lds, t->rows, st);
       }
       break;
     default:

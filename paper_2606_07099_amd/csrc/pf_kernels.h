@@ -66,6 +66,7 @@ struct SymOffsets {
   int bus_type, bus_blk, y_rp, y_ci, y_g, y_b;
   int rp, ci, diag, fill4, tail_pos, tail_split, tail_mask;
   int f_ptr, f_blob, fs_ptr, fs_blob, bs_ptr, bs_blob;   // level metadata chunks
+  int r_ptr, r_blob, fill_col, fill_gb;   // row-by-row factorisation: chunks; per stored block column bus | flags, Y entry
   int newton_bytes;
   // [newton_bytes, adj_bytes): what the LDS-resident adjoint reads besides
   int ut_ptr, ut_blob, lt_ptr, lt_blob, tt_ptr, tt_pairs, y_tr;
@@ -73,6 +74,7 @@ struct SymOffsets {
   int tail_cblk;                          // position of each compact tail block (LDS copy of the tail)
   int tail_prog;                          // per-pivot elimination program of the tail (LDS tail copy)
   int ord_p, ord_q;                       // paper-order positions (exports)
+  int lu_pos;                             // storage index of each LU position (exports)
   int total_bytes;
 };
 
@@ -82,6 +84,7 @@ struct Dims {
   int nlev_f, nlev_fs, nlev_bs;   // factor-task, forward and backward levels outside the tail
   int tail_t, tail_base;          // dense tail rows [tail_base, tail_base + tail_t)
   int nch_f, nch_fs, nch_bs;      // metadata chunks of the factor, forward and backward levels
+  int nch_r;                      // metadata chunks of the row-by-row factorisation
   int nch_ut, nch_lt;             // metadata chunks of the transposed solves
   int chunk_ints;                 // largest chunk (int32 words), staged after the LDS scratch
   int tail_nblk;                  // blocks of the tail rows in tail columns (LDS tail copy)
@@ -89,6 +92,8 @@ struct Dims {
   int tail_prog_ints;             // words of the tail program
   int tail_prog_prefix;           // its records, step and column words: kept in LDS
   int tail_prog_lds;              // 1: its update words staged in the metadata area, 0: read in place
+  int tail_off;                   // HBM-resident slices: byte offset of the LDS tail copy, or of the row buffers
+                                  // of the row-by-row factorisation (which runs before the tail is copied)
   int y_lds_off;                  // HBM-resident slices: byte offset of y in LDS (0: y stays in HBM)
 };
 
@@ -107,6 +112,10 @@ struct StateLayout {
   int o_y, o_lu, o_dinv;
   int st;  // T elements per scenario
 };
+
+// flags of a stored block's fill_col word (the rest is its column's bus)
+constexpr int kFillNone = 1 << 30;   // fill-in: no Y_bus entry
+constexpr int kFillPv = 1 << 29;     // the column's bus is a PV bus
 
 struct KParams {
   Dims dims;
@@ -144,12 +153,14 @@ constexpr int res_newton_threads() { return kResThreads; }
 inline int res_newton_threads(bool) { return kResThreads; }
 
 // slice = scenarios per workgroup: 1, 2 or 4 when LDS-resident, up to 16 otherwise.
+// rows: HBM-resident slices factor row by row (else by levels, one scenario per slice).
 hipError_t launch_newton(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds,
-                         bool lds_res, hipStream_t st);
+                         bool lds_res, bool rows, hipStream_t st);
 // slice > 0: LDS-resident adjoint slices of that width (kResThreads threads);
 // slice < 0: HBM-resident slices of width -slice reading the forward solve's
 // slice workspace (at most 1024 threads)
-hipError_t launch_adjoint(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds, hipStream_t st);
+hipError_t launch_adjoint(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds, bool rows,
+                          hipStream_t st);
 hipError_t launch_jacobian_dense(const KParams& kp, int grid, hipStream_t st);
 // Step-2 recovery of the generation block for kp.count scenarios
 hipError_t launch_recover(const KParams& kp, hipStream_t st);

@@ -21,6 +21,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "symbolic.h"
+
 namespace sable {
 
 // ----------------------------------------------------------------------------
@@ -111,6 +113,21 @@ __device__ __forceinline__ Blk<T> mul(const Blk<T>& x, const Blk<T>& y) {
 __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double recip(double x) { return 1.0 / x; }
 
+// inverse of a pivot block; flags the scenario when a pivot of the block (a,
+// then the Schur complement d - c b / a) does not stand out of its scale or the
+// inverse is not finite
+template <typename T>
+__device__ __forceinline__ Blk<T> pivot_inverse(const Blk<T>& Dk, int* piv, int s) {
+  const T det = Dk.a * Dk.d - Dk.b * Dk.c;
+  const T inv = recip(det);
+  const T eps = sizeof(T) == 8 ? T(1e-14) : T(1e-7);
+  const bool zero = !(fabs(Dk.a) > eps * (fabs(Dk.a) + fabs(Dk.b))) ||
+                    !(fabs(det) > eps * fabs(Dk.a) * (fabs(Dk.c) + fabs(Dk.d))) ||
+                    !isfinite(inv);
+  if (zero) piv[s] = 1;
+  return {Dk.d * inv, -Dk.b * inv, -Dk.c * inv, Dk.a * inv};
+}
+
 // interleaved indexing inside a slice of S scenarios
 template <int S> __device__ __forceinline__ int sI(int i, int s) { return i * S + s; }
 template <int S> __device__ __forceinline__ int sP(int a, int s) { return (a * S + s) * 2; }
@@ -126,7 +143,9 @@ struct Sym {
   const unsigned* tail_mask;
   const int *y_tr, *ord_p, *ord_q;
   const int *f_ptr, *f_blob, *fs_ptr, *fs_blob, *bs_ptr, *bs_blob;
-  const int* tail_cblk;
+  const int *r_ptr, *r_blob, *fill_col;
+  const double2* fill_gb;
+  const int *tail_cblk, *lu_pos;
 };
 
 __device__ __forceinline__ Sym bind_sym(const unsigned char* nb, const unsigned char* g,
@@ -152,6 +171,11 @@ __device__ __forceinline__ Sym bind_sym(const unsigned char* nb, const unsigned 
   m.fs_blob = I(nb, o.fs_blob);
   m.bs_ptr = I(nb, o.bs_ptr);
   m.bs_blob = I(nb, o.bs_blob);
+  m.r_ptr = I(g, o.r_ptr);
+  m.r_blob = I(g, o.r_blob);
+  m.fill_col = I(g, o.fill_col);
+  m.fill_gb = reinterpret_cast<const double2*>(g + o.fill_gb);
+  m.lu_pos = I(g, o.lu_pos);
   m.tail_prog = I(g, o.tail_prog);
   m.y_tr = I(g, o.y_tr);   // LDS-resident adjoint slices rebind it to their LDS copy
   m.ord_p = I(g, o.ord_p);
@@ -683,16 +707,7 @@ __device__ __forceinline__ void phase_factor(const Sym& m, const Dims& D, St<T>&
           // step, updated by this lane, so only the other lanes' targets of
           // earlier steps (several steps) need the fence before it is read
           if (se - tk.w > 1 && E > 1) wave_order<RES>();
-          const Blk<T> Dk = ld_blk(W + sB<S>(tk.z, s));
-          const T det = Dk.a * Dk.d - Dk.b * Dk.c;
-          const T inv = recip(det);
-          const Blk<T> Di = {Dk.d * inv, -Dk.b * inv, -Dk.c * inv, Dk.a * inv};
-          const T eps = sizeof(T) == 8 ? T(1e-14) : T(1e-7);
-          const bool zero = !(fabs(Dk.a) > eps * (fabs(Dk.a) + fabs(Dk.b))) ||
-                            !(fabs(det) > eps * fabs(Dk.a) * (fabs(Dk.c) + fabs(Dk.d))) ||
-                            !isfinite(inv);
-          if (zero) piv[s] = 1;
-          st_blk(c.dinv + sB<S>(a, s), Di);
+          st_blk(c.dinv + sB<S>(a, s), pivot_inverse(ld_blk(W + sB<S>(tk.z, s)), piv, s));
         }
         if (fwd) { c.y[sP<S>(a, s)] = y0; c.y[sP<S>(a, s) + 1] = y1; }
       }
@@ -701,13 +716,169 @@ __device__ __forceinline__ void phase_factor(const Sym& m, const Dims& D, St<T>&
   }
 }
 
+// Block LU of HBM-resident slices row by row (up-looking by levels, split
+// storage, pivot blocks in L): the lanes of a row form its Jacobian blocks in a
+// buffer in LDS, apply its elimination steps there in pivot order,
+//   A_aj -= A_ak U_kj,  y_a -= A_ak y_k  (U_k* and y_k already scaled),
+// then scale its U part and right-hand side by the inverse of its pivot block
+// and write the finished row once.  Rows of a level only read rows of lower
+// levels; the rows of the dense tail come last, stop before their pivots inside
+// it and are left unscaled.  With fill_only the Jacobian blocks are written as
+// they are.
+//
+// The state of a large grid's slices is far beyond the caches, so with many
+// scenarios per slice the factorisation is bound by the bytes it moves: here
+// per block one write and per update one read of a U block, with the Jacobian
+// values formed on the way.  By levels in place (a pass that writes all
+// Jacobian blocks, then every update reading and writing its target in device
+// memory) a factorisation moved about twice as much.  Jacobian values and
+// levelled factorisation of a 1354-bus x4096 launch, 5 updates: FP64 7.5 ms by
+// levels, 4.1 here; FP32 factors 3.7 and 2.7 ms (4.7 TB/s is a large copy's
+// rate; 16 scenarios' U blocks, values and state take 3.9 and 2.2 ms at it).
+// The U blocks and right-hand sides of the next kAhead steps are in flight (a
+// device-memory load takes several steps), the first ones from before the
+// Jacobian gathers; a step's metadata is read from LDS one step ahead.
+//
+// A group of lanes owns a row: lanes = scenarios x entries of the U row; a
+// group of several wavefronts gives each its own scenarios, so that the steps
+// of a row never need a barrier (LDS operations of a wavefront stay in order).
+template <typename T, int S>
+__device__ __forceinline__ void phase_rows(const Sym& m, const Dims& D, St<T>& c, int tid, int nt, bool fwd,
+                                           bool fill_only, int* piv, unsigned char* lds, T* buf) {
+  constexpr int kAhead = sizeof(T) == 4 ? 4 : 2;
+  ChunkStager<true> stg(m.r_ptr, m.r_blob, D.nch_r, lds, tid, nt);
+  for (int ch = 0; ch < D.nch_r; ++ch) {
+    const int* h = stg.get(ch);
+    const int nrow = __builtin_amdgcn_readfirstlane(h[0]), nstep = __builtin_amdgcn_readfirstlane(h[1]);
+    const int geo = __builtin_amdgcn_readfirstlane(h[2]);
+    const int lr = geo & 255, lsw = geo >> 8;
+    const int4* rw = reinterpret_cast<const int4*>(h + 4);
+    const int4* st4 = rw + 2 * (nrow + 1);
+    const int* tg = reinterpret_cast<const int*>(st4 + nstep + 1);
+    const int gid = tid >> lr, ng = nt >> lr;
+    const int wl = lr < 6 ? lr : 6;                         // log2 lanes of the group in this wavefront
+    const int l = tid & ((1 << wl) - 1);
+    const int w = lr > 6 ? (tid >> 6) & ((1 << (lr - 6)) - 1) : 0;
+    const int s = (w << lsw) + (l & ((1 << lsw) - 1)), e = l >> lsw, E = 1 << (wl - lsw);
+    for (int ri = gid; ri < nrow && gid < ng; ri += ng) {
+      const int4 r0 = rw[2 * ri], r1 = rw[2 * ri + 1];   // bus, blocks, buffer, first step; row, L, U, L blocks
+      const int s0 = r0.w, se = fill_only ? s0 : rw[2 * ri + 2].w, n = r0.y;
+      const int nl = r1.w & (kRowPv - 1);
+      const bool fin = (r1.w & kRowFinal) != 0 && !fill_only;
+      T* W = buf + sB<S>(r0.z, 0);
+      auto at = [&](int j) { return j <= nl ? r1.y + j : r1.z + (j - nl - 1); };   // storage of the row's block j
+      // the loads of a step; past the row's end those of its last step again
+      Blk<T> U[kAhead];
+      T yk[kAhead][2];
+      auto fetch = [&](int i, Blk<T>& u, T (&y)[2]) {
+        i = i < se ? i : se - 1;
+        const int4 st = st4[i];
+        const int nu = st4[i + 1].w - st.w;
+        u = ld_blk(c.lu + sB<S>(st.z + (e < nu ? e : 0), s));
+        y[0] = c.y[sP<S>(st.y, s)];
+        y[1] = c.y[sP<S>(st.y, s) + 1];
+      };
+      // and a step's block of the row, U blocks and this lane's first target
+      int nq = 0, nn = 0, nx = 0;
+      auto meta = [&](int i) {
+        i = i < se ? i : se - 1;
+        const int4 st = st4[i];
+        nq = st.x;
+        nn = st4[i + 1].w - st.w;
+        nx = tg[st.w + (e < nn ? e : 0)];
+      };
+      if (s0 < se) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) fetch(s0 + u, U[u], yk[u]);
+        meta(s0);
+      }
+      // the row's Jacobian blocks
+      const int go = c.g(r0.x, s);
+      const double ei = c.e[go], fi = c.f[go];
+      for (int j = e; j < n; j += E) {
+        const int sp = at(j);
+        const int fc = m.fill_col[sp];
+        const double2 gb = m.fill_gb[sp];
+        const bool dg = j == nl;
+        FillIn q;
+        q.r = make_int4((fc & kFillNone) ? -1 : 0, 0, 0,
+                        (dg ? 1 : 0) | ((r1.w & kRowPv) ? 2 : 0) | ((fc & kFillPv) ? 4 : 0));
+        q.g = gb.x;
+        q.b = gb.y;
+        const int mo = c.g(fc & (kFillPv - 1), s);
+        q.x[0] = ei;
+        q.x[1] = fi;
+        q.x[2] = q.x[3] = 1.0;
+        q.x[4] = q.x[5] = 0.0;
+        if (dg) {
+          q.x[4] = c.ire[mo];
+          q.x[5] = c.iim[mo];
+        } else if (!(fc & kFillNone)) {
+          q.x[2] = c.e[mo];
+          q.x[3] = c.f[mo];
+        }
+        st_blk(W + sB<S>(j, s), fill_value<T, false>(q));
+      }
+      T y0 = T(0), y1 = T(0);
+      if (fwd) { y0 = c.y[sP<S>(r1.x, s)]; y1 = c.y[sP<S>(r1.x, s) + 1]; }
+      asm volatile("" ::: "memory");
+      for (int i = s0; i < se; i += kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          const Blk<T> Uk = U[u];
+          const T yk0 = yk[u][0], yk1 = yk[u][1];
+          fetch(i + kAhead + u, U[u], yk[u]);
+          if (i + u < se) {
+            const int q = nq, nu = nn;
+            T* x = W + sB<S>(nx, s);
+            meta(i + u + 1);
+            const Blk<T> L = ld_blk(W + sB<S>(q, s));
+            y0 -= L.a * yk0 + L.b * yk1;
+            y1 -= L.c * yk0 + L.d * yk1;
+            if (e < nu) {
+              Blk<T> v = ld_blk(x);
+              const Blk<T> LU = mul(L, Uk);
+              v.a -= LU.a; v.b -= LU.b; v.c -= LU.c; v.d -= LU.d;
+              st_blk(x, v);
+            }
+            for (int t = e + E; t < nu; t += E) {
+              const int4 st = st4[i + u];
+              const Blk<T> Ut = ld_blk(c.lu + sB<S>(st.z + t, s));
+              x = W + sB<S>(tg[st.w + t], s);
+              Blk<T> v = ld_blk(x);
+              const Blk<T> LU = mul(L, Ut);
+              v.a -= LU.a; v.b -= LU.b; v.c -= LU.c; v.d -= LU.d;
+              st_blk(x, v);
+            }
+          }
+          asm volatile("" ::: "memory");   // the next step reads what the lanes of this one wrote
+        }
+      }
+      Blk<T> Di = {T(1), T(0), T(0), T(1)};
+      if (fin) Di = pivot_inverse(ld_blk(W + sB<S>(nl, s)), piv, s);
+      for (int j = e; j < n; j += E) {
+        const Blk<T> v = ld_blk(W + sB<S>(j, s));
+        st_blk(c.lu + sB<S>(at(j), s), !fin || j < nl ? v : j == nl ? Di : mul(Di, v));
+      }
+      if (fwd && e == 0) {
+        c.y[sP<S>(r1.x, s)] = Di.a * y0 + Di.b * y1;
+        c.y[sP<S>(r1.x, s) + 1] = Di.c * y0 + Di.d * y1;
+      }
+      asm volatile("" ::: "memory");   // the group's next row reuses the buffer
+    }
+    __syncthreads();
+  }
+}
+
 // level-scheduled row solves of the rows outside the dense tail, rows and
 // their columns from the metadata chunks: forward (unit block-lower L, in
 // place in y) or backward (U with the inverted pivot blocks)
+// UNITU: the pivot blocks belong to L (row-by-row factorisation), so that the
+// forward pass multiplies by their inverses and the backward pass does not.
 // The backward pass can also hand its result to the FP64 correction of the
 // scenarios in `mask`: dxmode 1 sets dx = y, dxmode 2 adds y to dx (each row
 // is written once, by its lane of entry 0, so no separate copy pass is needed).
-template <typename T, int S, bool RES, bool LOWER>
+template <typename T, int S, bool RES, bool LOWER, bool UNITU>
 __device__ __forceinline__ void phase_solve(const Sym& m, const Dims& D, St<T>& c, int tid, int nt, int gmin,
                                             unsigned char* lds, int dxmode = 0, int mask = 0) {
   const int nch = LOWER ? D.nch_fs : D.nch_bs;
@@ -723,7 +894,7 @@ __device__ __forceinline__ void phase_solve(const Sym& m, const Dims& D, St<T>& 
     const int G = g.G;
     const int s = g.lane % S, e = g.lane / S, E = G / S;
     for (int ri = g.gid; ri < nrow; ri += g.ng) {
-      const int4 r = rw[ri];   // row, first position, -, first column
+      const int4 r = rw[ri];   // row, first position, index of its pivot inverse, first column
       const int a = r.x, n = rw[ri + 1].w - r.w;
       // the row's own right-hand side (and, backward, its pivot inverse and
       // the correction it adds to) are loaded before the dot product, so
@@ -734,7 +905,7 @@ __device__ __forceinline__ void phase_solve(const Sym& m, const Dims& D, St<T>& 
       if (e == 0) {
         ya0 = c.y[sP<S>(a, s)];
         ya1 = c.y[sP<S>(a, s) + 1];
-        if (!LOWER) Di = ld_blk(c.dinv + sB<S>(a, s));
+        if (LOWER == UNITU) Di = ld_blk(c.dinv + sB<S>(r.z, s));
         if (!LOWER && dxmode == 2) {
           dx0 = c.dx[sP<S>(a, s)];
           dx1 = c.dx[sP<S>(a, s) + 1];
@@ -771,14 +942,15 @@ __device__ __forceinline__ void phase_solve(const Sym& m, const Dims& D, St<T>& 
       s0 = group_sum<T, S>(s0, G);
       s1 = group_sum<T, S>(s1, G);
       if (e == 0) {
-        if (LOWER) {
-          c.y[sP<S>(a, s)] = ya0 - s0;
-          c.y[sP<S>(a, s) + 1] = ya1 - s1;
-        } else {
-          const T t0 = ya0 - s0, t1 = ya1 - s1;
-          const T x0 = Di.a * t0 + Di.b * t1, x1 = Di.c * t0 + Di.d * t1;
-          c.y[sP<S>(a, s)] = x0;
-          c.y[sP<S>(a, s) + 1] = x1;
+        T x0 = ya0 - s0, x1 = ya1 - s1;
+        if (LOWER == UNITU) {
+          const T t0 = x0, t1 = x1;
+          x0 = Di.a * t0 + Di.b * t1;
+          x1 = Di.c * t0 + Di.d * t1;
+        }
+        c.y[sP<S>(a, s)] = x0;
+        c.y[sP<S>(a, s) + 1] = x1;
+        if (!LOWER) {
           if (dxmode == 1) {
             c.dx[sP<S>(a, s)] = double(x0);
             c.dx[sP<S>(a, s) + 1] = double(x1);
@@ -837,18 +1009,18 @@ __device__ __forceinline__ void ltail_copy(const Sym& m, const Dims& D, St<T>& c
 }
 
 template <typename T, int S>
-__device__ __forceinline__ void ltail_store_dinv(const Dims& D, St<T>& c, const T* td, int tid, int nt) {
+__device__ __forceinline__ void ltail_store_dinv(const Sym& m, const Dims& D, St<T>& c, const T* td, int tid, int nt) {
   for (int q = tid; q < D.tail_t * S * 4; q += nt) {
     const int comp = q & 3, s = (q >> 2) % S, k = (q >> 2) / S;
-    c.dinv[sB<S>(D.tail_base + k, s) + comp] = td[tdB(k, s, D.tail_t) + comp];
+    c.dinv[sB<S>(m.tail_prog[8 * k + 7], s) + comp] = td[tdB(k, s, D.tail_t) + comp];
   }
 }
 
 template <typename T, int S>
-__device__ __forceinline__ void ltail_load_dinv(const Dims& D, St<T>& c, T* td, int tid, int nt) {
+__device__ __forceinline__ void ltail_load_dinv(const Sym& m, const Dims& D, St<T>& c, T* td, int tid, int nt) {
   for (int q = tid; q < D.tail_t * S * 4; q += nt) {
     const int comp = q & 3, s = (q >> 2) % S, k = (q >> 2) / S;
-    td[tdB(k, s, D.tail_t) + comp] = c.dinv[sB<S>(D.tail_base + k, s) + comp];
+    td[tdB(k, s, D.tail_t) + comp] = c.dinv[sB<S>(m.tail_prog[8 * k + 7], s) + comp];
   }
 }
 
@@ -1540,8 +1712,9 @@ __device__ __forceinline__ void phase_set_state(const Dims& D, St<T>& c, int tid
 // ----------------------------------------------------------------------------
 // the Newton kernel: one workgroup = one slice of S scenarios
 
-template <typename T, bool RES, int S>
+template <typename T, bool RES, int S, bool ROWS>
 __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton(KParams kp) {
+  static_assert(!(RES && ROWS), "row-by-row factorisation: HBM-resident slices");
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, nt = blockDim.x;
   PhaseClock pc(tid);
@@ -1611,10 +1784,12 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
   const int gmin = kp.gmin > S ? kp.gmin : S;
   const int wv = tid >> 6, ln = tid & 63;   // LDS-resident tails: wavefront wv <-> scenario wv
   unsigned char* stg = smem + kScratchBytes; // HBM-resident slices: staged level metadata
-  T* tl = reinterpret_cast<T*>(smem + kScratchBytes + 4 * (size_t)kp.dims.chunk_ints);   // HBM: LDS tail
+  // HBM: the tail program's prefix, then the LDS tail, which shares its place
+  // with the row buffers of the factorisation that runs before it
+  int* tq = reinterpret_cast<int*>(stg + 4 * (size_t)kp.dims.chunk_ints);
+  T* tl = reinterpret_cast<T*>(smem + kp.dims.tail_off);
   T* td = tl + (size_t)kp.dims.tail_nbs * S * 4;
   T* ty = td + (size_t)kp.dims.tail_t * S * 4;
-  int* tq = reinterpret_cast<int*>(ty + (size_t)kp.dims.tail_t * S * 2);   // HBM: tail program prefix
   if constexpr (!RES) {
     for (int q = tid; q < kp.dims.tail_prog_prefix; q += nt) tq[q] = m.tail_prog[q];
     // the right-hand side / solution of the triangular solves, when the
@@ -1646,7 +1821,8 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
     }
     if (kp.mode == MODE_EVAL_MISMATCH || kp.mode == MODE_EVAL_FACTOR) break;
     if (kp.mode == MODE_EVAL_FILL) {
-      phase_fill<T, S, RES>(m, D, c, tid, nt);
+      if constexpr (ROWS) phase_rows<T, S>(m, D, c, tid, nt, false, true, piv, stg, tl);
+      else phase_fill<T, S, RES>(m, D, c, tid, nt);
       break;
     }
     if (!act) break;
@@ -1654,10 +1830,14 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
     // as they write them; a slice of one scenario scatters each of those
     // stores to its own line, on the critical path of a level, so it updates
     // dx in a streaming pass of its own
-    phase_fill<T, S, RES>(m, D, c, tid, nt);
-    pc.mark(PH_FILL);
     pc.count(PH_NEWTON_STEPS);
-    phase_factor<T, S, RES>(m, D, c, tid, nt, gmin, true, piv, stg);
+    if constexpr (ROWS) {
+      phase_rows<T, S>(m, D, c, tid, nt, true, false, piv, stg, tl);
+    } else {
+      phase_fill<T, S, RES>(m, D, c, tid, nt);
+      pc.mark(PH_FILL);
+      phase_factor<T, S, RES>(m, D, c, tid, nt, gmin, true, piv, stg);
+    }
     pc.mark(PH_FACTOR_LEVELS);
     if constexpr (RES) {
       if (wv < S) rt_factor<T, S>(m, D, c, wv, ln, true, piv, R);
@@ -1682,7 +1862,7 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
     }
     __syncthreads();
     pc.mark(PH_BSOLVE_TAIL);
-    phase_solve<T, S, RES, false>(m, D, c, tid, nt, gmin, stg, dx_set);   // dx = y as well
+    phase_solve<T, S, RES, false, ROWS>(m, D, c, tid, nt, gmin, stg, dx_set);   // dx = y as well
     pc.mark(PH_BSOLVE_LEVELS);
     // slices that keep dx out of the backward solves hand the last solve's
     // y to dx only when a later pass reads dx: the state update reads dx
@@ -1719,7 +1899,7 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
           if (!ref) break;
         }
         pc.count(PH_REFINE_STEPS);
-        phase_solve<T, S, RES, true>(m, D, c, tid, nt, gmin, stg);
+        phase_solve<T, S, RES, true, ROWS>(m, D, c, tid, nt, gmin, stg);
         pc.mark(PH_REFINE_FSOLVE_LEVELS);
         if constexpr (RES) {
           if (wv < S) {
@@ -1731,7 +1911,7 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
         }
         __syncthreads();
         pc.mark(PH_REFINE_TAIL);
-        phase_solve<T, S, RES, false>(m, D, c, tid, nt, gmin, stg, dx_add, ref);   // dx += y as well
+        phase_solve<T, S, RES, false, ROWS>(m, D, c, tid, nt, gmin, stg, dx_add, ref);   // dx += y as well
         pc.mark(PH_REFINE_BSOLVE_LEVELS);
         if (!fuse) {
           pend = 2;
@@ -1799,8 +1979,8 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
     // the filled LU values of each scenario, block by block (row-major 2x2)
     const size_t nv = 4 * (size_t)D.nnzb;
     for (int q = tid; q < 4 * D.nnzb * S; q += nt) {
-      const int blk = q >> 2, b = slice * S + blk % S;
-      if (b < kp.count) kp.out[(size_t)b * nv + 4 * (blk / S) + (q & 3)] = double(c.lu[q]);
+      const int p = (q >> 2) / S, s = (q >> 2) % S, b = slice * S + s;
+      if (b < kp.count) kp.out[(size_t)b * nv + 4 * p + (q & 3)] = double(c.lu[sB<S>(m.lu_pos[p], s) + (q & 3)]);
     }
   } else if (kp.mode == MODE_EVAL_MISMATCH || kp.mode == MODE_EVAL_STEP) {
     const int nj = D.nj;
@@ -1823,8 +2003,12 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
   const bool keep = (kp.mode == MODE_SOLVE && kp.keep) || kp.mode == MODE_EVAL_FACTOR;
   if (keep) {
     if (tid < S) piv[tid] = 0;
-    phase_fill<T, S, RES>(m, D, c, tid, nt);
-    phase_factor<T, S, RES>(m, D, c, tid, nt, gmin, false, piv, stg);
+    if constexpr (ROWS) {
+      phase_rows<T, S>(m, D, c, tid, nt, false, false, piv, stg, tl);
+    } else {
+      phase_fill<T, S, RES>(m, D, c, tid, nt);
+      phase_factor<T, S, RES>(m, D, c, tid, nt, gmin, false, piv, stg);
+    }
     if constexpr (RES) {
       if (wv < S) {
         rt_factor<T, S>(m, D, c, wv, ln, false, piv, R);
@@ -1837,7 +2021,8 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
       ltail_factor<T, S>(D, c, tl, td, ty, tq, tp, tid, nt, false, piv);
       __syncthreads();
       ltail_copy<T, S>(m, D, c, tl, tid, nt, true);
-      ltail_store_dinv<T, S>(D, c, td, tid, nt);
+      __syncthreads();   // an inverse may take its pivot block's place
+      ltail_store_dinv<T, S>(m, D, c, td, tid, nt);
     }
     __syncthreads();
     if (tid < S && s_st[tid] == 0 && piv[tid]) s_st[tid] = 3;
@@ -1909,8 +2094,8 @@ __device__ __forceinline__ AdjSym bind_adj(const unsigned char* b, const SymOffs
 
 // U^T w = g by forward levels (UT) or L^T l = w by backward levels, rows
 // outside the tail, in place in y; entries are (column, position of the
-// transposed block) pairs
-template <typename T, int S, bool RES, bool UT>
+// transposed block) pairs; UNITU as in phase_solve
+template <typename T, int S, bool RES, bool UT, bool UNITU>
 __device__ __forceinline__ void phase_tsolve(const AdjSym& a, const Dims& D, St<T>& c, int tid, int nt, int gmin,
                                              unsigned char* lds) {
   const int nch = UT ? D.nch_ut : D.nch_lt;
@@ -1926,16 +2111,16 @@ __device__ __forceinline__ void phase_tsolve(const AdjSym& a, const Dims& D, St<
     const int G = g.G;
     const int s = g.lane % S, e = g.lane / S, E = G / S;
     for (int ri = g.gid; ri < nrow; ri += g.ng) {
-      const int4 r = rw[ri];   // row, -, -, first pair
+      const int4 r = rw[ri];   // row, -, index of its pivot inverse, first pair
       const int row = r.x, n = rw[ri + 1].w - r.w;
-      // the row's own right-hand side (and, for U^T, its pivot inverse)
+      // the row's own right-hand side (and the pivot inverse of the pass that uses it)
       // loaded before the dot product, whose latency they then overlap
       T ya0 = T(0), ya1 = T(0);
       Blk<T> Di = {T(0), T(0), T(0), T(0)};
       if (e == 0) {
         ya0 = c.y[sP<S>(row, s)];
         ya1 = c.y[sP<S>(row, s) + 1];
-        if (UT) Di = ld_blk(c.dinv + sB<S>(row, s));
+        if (UT != UNITU) Di = ld_blk(c.dinv + sB<S>(r.z, s));
       }
       T s0 = T(0), s1 = T(0);
       int j = e;
@@ -1965,7 +2150,7 @@ __device__ __forceinline__ void phase_tsolve(const AdjSym& a, const Dims& D, St<
       s0 = group_sum<T, S>(s0, G);
       s1 = group_sum<T, S>(s1, G);
       if (e == 0) {
-        if (UT) {
+        if (UT != UNITU) {
           const T t0 = ya0 - s0, t1 = ya1 - s1;
           c.y[sP<S>(row, s)] = Di.a * t0 + Di.c * t1;
           c.y[sP<S>(row, s) + 1] = Di.b * t0 + Di.d * t1;
@@ -2207,7 +2392,7 @@ __device__ __forceinline__ void phase_adj_residual_s(const Sym& m, const Dims& D
   __syncthreads();
 }
 
-template <typename T, bool RES, int S>
+template <typename T, bool RES, int S, bool ROWS>
 __global__ void __launch_bounds__(RES ? kResThreads : 1024) k_adjoint_slice(KParams kp) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, nt = blockDim.x;
@@ -2275,12 +2460,12 @@ __global__ void __launch_bounds__(RES ? kResThreads : 1024) k_adjoint_slice(KPar
   T* td = nullptr;
   int* tq = nullptr;
   if constexpr (!RES) {
-    tl = reinterpret_cast<T*>(smem + kScratchBytes + 4 * (size_t)D.chunk_ints);
+    tl = reinterpret_cast<T*>(smem + D.tail_off);
     td = tl + (size_t)D.tail_nbs * S * 4;
-    tq = reinterpret_cast<int*>(td + (size_t)D.tail_t * S * 4 + (size_t)D.tail_t * S * 2);
+    tq = reinterpret_cast<int*>(stg + 4 * (size_t)D.chunk_ints);
     for (int q = tid; q < D.tail_prog_prefix; q += nt) tq[q] = m.tail_prog[q];
     ltail_copy<T, S>(m, D, c, tl, tid, nt, false);
-    ltail_load_dinv<T, S>(D, c, td, tid, nt);
+    ltail_load_dinv<T, S>(m, D, c, td, tid, nt);
   }
   if (tid < S) {
     const int b = slice * S + tid;
@@ -2326,7 +2511,7 @@ __global__ void __launch_bounds__(RES ? kResThreads : 1024) k_adjoint_slice(KPar
   __syncthreads();
   const int gmin = S > 4 ? S : 4;
   auto solve = [&]() {
-    phase_tsolve<T, S, RES, true>(as, D, c, tid, nt, gmin, stg);
+    phase_tsolve<T, S, RES, true, ROWS>(as, D, c, tid, nt, gmin, stg);
     if constexpr (RES) {
       for (int s = wv; s < S; s += nw) rt_tsolve<T, S>(m, as, D, c, s, ln);
     } else {
@@ -2335,7 +2520,7 @@ __global__ void __launch_bounds__(RES ? kResThreads : 1024) k_adjoint_slice(KPar
       for (int s = wv; s < S; s += nw) rt_tsolve<T, S>(m, as, D, c, s, ln, tl, td, tq, pa, P);
     }
     __syncthreads();
-    phase_tsolve<T, S, RES, false>(as, D, c, tid, nt, gmin, stg);
+    phase_tsolve<T, S, RES, false, ROWS>(as, D, c, tid, nt, gmin, stg);
   };
   solve();
   for (int q = tid; q < 2 * nb * S; q += nt) c.dx[q] = double(c.y[q]);
@@ -2486,23 +2671,26 @@ __global__ void __launch_bounds__(256) k_jacobian_dense(KParams kp) {
 
 template <typename T>
 static hipError_t launch_newton_t(const KParams& kp, int slice, int grid, int nt, size_t lds,
-                                  bool res, hipStream_t st) {
+                                  bool res, bool rows, hipStream_t st) {
   dim3 g(grid), b(nt);
   if (res && (nt != res_newton_threads<T>() || slice > kResMaxSlice)) return hipErrorInvalidValue;
-  if (!res) {
+  if (!res && !rows) {
+    if (slice != 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_newton<T, false, 1, false>), g, b, lds, st, kp);
+  } else if (!res) {
     switch (slice) {
-      case 1: hipLaunchKernelGGL((k_newton<T, false, 1>), g, b, lds, st, kp); break;
-      case 2: hipLaunchKernelGGL((k_newton<T, false, 2>), g, b, lds, st, kp); break;
-      case 4: hipLaunchKernelGGL((k_newton<T, false, 4>), g, b, lds, st, kp); break;
-      case 8: hipLaunchKernelGGL((k_newton<T, false, 8>), g, b, lds, st, kp); break;
-      case 16: hipLaunchKernelGGL((k_newton<T, false, 16>), g, b, lds, st, kp); break;
+      case 1: hipLaunchKernelGGL((k_newton<T, false, 1, true>), g, b, lds, st, kp); break;
+      case 2: hipLaunchKernelGGL((k_newton<T, false, 2, true>), g, b, lds, st, kp); break;
+      case 4: hipLaunchKernelGGL((k_newton<T, false, 4, true>), g, b, lds, st, kp); break;
+      case 8: hipLaunchKernelGGL((k_newton<T, false, 8, true>), g, b, lds, st, kp); break;
+      case 16: hipLaunchKernelGGL((k_newton<T, false, 16, true>), g, b, lds, st, kp); break;
       default: return hipErrorInvalidValue;
     }
   } else {
     switch (slice) {
-      case 1: hipLaunchKernelGGL((k_newton<T, true, 1>), g, b, lds, st, kp); break;
-      case 2: hipLaunchKernelGGL((k_newton<T, true, 2>), g, b, lds, st, kp); break;
-      case 4: hipLaunchKernelGGL((k_newton<T, true, 4>), g, b, lds, st, kp); break;
+      case 1: hipLaunchKernelGGL((k_newton<T, true, 1, false>), g, b, lds, st, kp); break;
+      case 2: hipLaunchKernelGGL((k_newton<T, true, 2, false>), g, b, lds, st, kp); break;
+      case 4: hipLaunchKernelGGL((k_newton<T, true, 4, false>), g, b, lds, st, kp); break;
       default: return hipErrorInvalidValue;
     }
   }
@@ -2510,44 +2698,53 @@ static hipError_t launch_newton_t(const KParams& kp, int slice, int grid, int nt
 }
 
 hipError_t launch_newton(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds,
-                         bool lds_res, hipStream_t st) {
-  return fp32 ? launch_newton_t<float>(kp, slice, grid, nt, lds, lds_res, st)
-              : launch_newton_t<double>(kp, slice, grid, nt, lds, lds_res, st);
+                         bool lds_res, bool rows, hipStream_t st) {
+  return fp32 ? launch_newton_t<float>(kp, slice, grid, nt, lds, lds_res, rows, st)
+              : launch_newton_t<double>(kp, slice, grid, nt, lds, lds_res, rows, st);
 }
 
 template <typename T>
-static hipError_t launch_adjoint_hbm_t(const KParams& kp, int slice, int grid, int nt, size_t lds, hipStream_t st);
+static hipError_t launch_adjoint_hbm_t(const KParams& kp, int slice, int grid, int nt, size_t lds, bool rows,
+                                       hipStream_t st);
 
 template <typename T>
-static hipError_t launch_adjoint_t(const KParams& kp, int slice, int grid, int nt, size_t lds, hipStream_t st) {
-  if (slice < 0) return launch_adjoint_hbm_t<T>(kp, -slice, grid, nt, lds, st);
+static hipError_t launch_adjoint_t(const KParams& kp, int slice, int grid, int nt, size_t lds, bool rows,
+                                   hipStream_t st) {
+  if (slice < 0) return launch_adjoint_hbm_t<T>(kp, -slice, grid, nt, lds, rows, st);
   if (nt != kResThreads) return hipErrorInvalidValue;
   switch (slice) {
-    case 1: hipLaunchKernelGGL((k_adjoint_slice<T, true, 1>), dim3(grid), dim3(nt), lds, st, kp); break;
-    case 2: hipLaunchKernelGGL((k_adjoint_slice<T, true, 2>), dim3(grid), dim3(nt), lds, st, kp); break;
-    case 4: hipLaunchKernelGGL((k_adjoint_slice<T, true, 4>), dim3(grid), dim3(nt), lds, st, kp); break;
+    case 1: hipLaunchKernelGGL((k_adjoint_slice<T, true, 1, false>), dim3(grid), dim3(nt), lds, st, kp); break;
+    case 2: hipLaunchKernelGGL((k_adjoint_slice<T, true, 2, false>), dim3(grid), dim3(nt), lds, st, kp); break;
+    case 4: hipLaunchKernelGGL((k_adjoint_slice<T, true, 4, false>), dim3(grid), dim3(nt), lds, st, kp); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 template <typename T>
-static hipError_t launch_adjoint_hbm_t(const KParams& kp, int slice, int grid, int nt, size_t lds, hipStream_t st) {
+static hipError_t launch_adjoint_hbm_t(const KParams& kp, int slice, int grid, int nt, size_t lds, bool rows,
+                                       hipStream_t st) {
   if (nt > 1024) return hipErrorInvalidValue;
+  if (!rows) {
+    if (slice != 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_adjoint_slice<T, false, 1, false>), dim3(grid), dim3(nt), lds, st, kp);
+    return hipGetLastError();
+  }
   switch (slice) {
-    case 1: hipLaunchKernelGGL((k_adjoint_slice<T, false, 1>), dim3(grid), dim3(nt), lds, st, kp); break;
-    case 2: hipLaunchKernelGGL((k_adjoint_slice<T, false, 2>), dim3(grid), dim3(nt), lds, st, kp); break;
-    case 4: hipLaunchKernelGGL((k_adjoint_slice<T, false, 4>), dim3(grid), dim3(nt), lds, st, kp); break;
-    case 8: hipLaunchKernelGGL((k_adjoint_slice<T, false, 8>), dim3(grid), dim3(nt), lds, st, kp); break;
-    case 16: hipLaunchKernelGGL((k_adjoint_slice<T, false, 16>), dim3(grid), dim3(nt), lds, st, kp); break;
+    case 1: hipLaunchKernelGGL((k_adjoint_slice<T, false, 1, true>), dim3(grid), dim3(nt), lds, st, kp); break;
+    case 2: hipLaunchKernelGGL((k_adjoint_slice<T, false, 2, true>), dim3(grid), dim3(nt), lds, st, kp); break;
+    case 4: hipLaunchKernelGGL((k_adjoint_slice<T, false, 4, true>), dim3(grid), dim3(nt), lds, st, kp); break;
+    case 8: hipLaunchKernelGGL((k_adjoint_slice<T, false, 8, true>), dim3(grid), dim3(nt), lds, st, kp); break;
+    case 16: hipLaunchKernelGGL((k_adjoint_slice<T, false, 16, true>), dim3(grid), dim3(nt), lds, st, kp); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_adjoint(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds, hipStream_t st) {
-  return fp32 ? launch_adjoint_t<float>(kp, slice, grid, nt, lds, st)
-              : launch_adjoint_t<double>(kp, slice, grid, nt, lds, st);
+hipError_t launch_adjoint(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds, bool rows,
+                          hipStream_t st) {
+  return fp32 ? launch_adjoint_t<float>(kp, slice, grid, nt, lds, rows, st)
+              : launch_adjoint_t<double>(kp, slice, grid, nt, lds, rows, st);
 }
 
 hipError_t launch_recover(const KParams& kp, hipStream_t st) {
@@ -2569,22 +2766,24 @@ static hipError_t set_lds_t(int max_lds) {
     hipError_t r = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
     if (r != hipSuccess) e = r;
   };
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 1>));
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 2>));
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 4>));
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 8>));
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 16>));
-  set(reinterpret_cast<const void*>(&k_newton<T, true, 1>));
-  set(reinterpret_cast<const void*>(&k_newton<T, true, 2>));
-  set(reinterpret_cast<const void*>(&k_newton<T, true, 4>));
-  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 1>));
-  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 2>));
-  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 4>));
-  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 1>));
-  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 2>));
-  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 4>));
-  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 8>));
-  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 16>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 1, false>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 1, true>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 2, true>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 4, true>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 8, true>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 16, true>));
+  set(reinterpret_cast<const void*>(&k_newton<T, true, 1, false>));
+  set(reinterpret_cast<const void*>(&k_newton<T, true, 2, false>));
+  set(reinterpret_cast<const void*>(&k_newton<T, true, 4, false>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 1, false>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 2, false>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 4, false>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 1, false>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 1, true>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 2, true>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 4, true>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 8, true>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 16, true>));
   return e;
 }
 

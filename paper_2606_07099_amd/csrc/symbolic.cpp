@@ -40,8 +40,132 @@ int32_t find_sorted(const int32_t* first, const int32_t* last, int32_t key) {
 
 }  // namespace
 
-int build_level_chunks(const Symbolic& S, int32_t budget_ints, LevelChunks& out, std::string& err) {
+LuStorage storage_by_position(const Symbolic& S) {
+  LuStorage st;
+  st.pos.resize(S.nnzb());
+  st.dinv.resize(S.nb);
+  std::iota(st.pos.begin(), st.pos.end(), 0);
+  std::iota(st.dinv.begin(), st.dinv.end(), 0);
+  return st;
+}
+
+LuStorage storage_split(const Symbolic& S) {
+  LuStorage st;
+  st.split = true;
+  st.pos.resize(S.nnzb());
+  st.dinv.resize(S.nb);
+  int32_t k = 0;
+  for (int32_t a = 0; a < S.nb; ++a) {
+    for (int32_t p = S.rp[a]; p <= S.diag[a]; ++p) st.pos[p] = k++;
+    st.dinv[a] = k - 1;
+  }
+  for (int32_t a = 0; a < S.nb; ++a)
+    for (int32_t p = S.diag[a] + 1; p < S.rp[a + 1]; ++p) st.pos[p] = k++;
+  return st;
+}
+
+int build_row_chunks(const Symbolic& S, const LuStorage& st, int32_t slice, int32_t threads,
+                     int64_t buffer_blocks, int32_t budget_ints, RowChunks& out, std::string& err) {
+  out = RowChunks{};
+  const int32_t nb = S.nb, tb = S.tail_base;
+  auto len = [&](int32_t a) { return S.rp[a + 1] - S.rp[a]; };
+  // elimination steps of a row: its L blocks with a pivot outside the tail
+  auto steps = [&](int32_t a) { return (a < tb ? S.diag[a] : S.tail_split[a - tb]) - S.rp[a]; };
+  auto targets = [&](int32_t a) {
+    int32_t n = 0;
+    for (int32_t p = S.rp[a]; p < S.rp[a] + steps(a); ++p) n += S.rp[S.ci[p] + 1] - S.diag[S.ci[p]] - 1;
+    return n;
+  };
+  auto u_at = [&](int32_t a) { return S.diag[a] + 1 < S.rp[a + 1] ? st.pos[S.diag[a] + 1] : 0; };
+  int32_t lg_slice = 0, lg_threads = 0;
+  while ((1 << (lg_slice + 1)) <= slice) ++lg_slice;
+  while ((2 << lg_threads) <= threads) ++lg_threads;
+  const int32_t lg_min = std::max(lg_slice, 2);               // at least one lane per scenario, four per row
+  const int32_t lg_max = std::min(6 + lg_slice, lg_threads);  // at least one scenario per wavefront
+  std::vector<std::vector<int32_t>> groups;
+  for (size_t h = 0; h + 1 < S.lev_l_ptr.size(); ++h) {
+    std::vector<int32_t> rows;
+    for (int32_t q = S.lev_l_ptr[h]; q < S.lev_l_ptr[h + 1]; ++q)
+      if (S.lev_l_rows[q] < tb) rows.push_back(S.lev_l_rows[q]);
+    if (!rows.empty()) groups.push_back(rows);
+  }
+  if (tb < nb) {
+    groups.emplace_back();
+    for (int32_t a = tb; a < nb; ++a) groups.back().push_back(a);
+  }
+  for (auto& rows : groups) {
+    std::stable_sort(rows.begin(), rows.end(), [&](int32_t x, int32_t y) { return len(x) > len(y); });
+    for (size_t r0 = 0; r0 < rows.size();) {
+      // as many rows as the metadata budget takes
+      size_t r1 = r0;
+      int64_t words = 4 + 8 + 4 + 3;
+      while (r1 < rows.size()) {
+        const int64_t need = 8 + 4 * (int64_t)steps(rows[r1]) + targets(rows[r1]);
+        if (words + need > budget_ints) break;
+        words += need;
+        ++r1;
+      }
+      if (r1 == r0) { err = "template: a row of the factorisation exceeds the metadata chunk budget"; return PF_EINVAL; }
+      // the widest groups that give every row one; wider ones, then fewer
+      // rows, while the buffers of the groups do not fit
+      int32_t lg = lg_max;
+      int64_t area = 0;
+      while (true) {
+        const size_t n = r1 - r0;
+        lg = lg_max;
+        while (lg > lg_min && (size_t)(threads >> lg) < n) --lg;
+        auto fits = [&](int32_t l) {
+          area = 0;
+          for (size_t i = 0; i < std::min<size_t>(n, threads >> l); ++i)
+            area += len(rows[r0 + i]);
+          return area <= buffer_blocks;
+        };
+        while (lg < lg_max && !fits(lg)) ++lg;
+        if (fits(lg)) break;
+        if (n == 1) { err = "template: a row of the factorisation exceeds the row buffers"; return PF_EINVAL; }
+        r1 = r0 + (n + 1) / 2;
+      }
+      out.max_buffer = std::max(out.max_buffer, area);
+      const size_t ng = threads >> lg;
+      std::vector<int32_t> rec, stp, tgt, off;
+      for (size_t i = 0, o = 0; i < std::min(ng, r1 - r0); ++i) {
+        off.push_back((int32_t)o);
+        o += len(rows[r0 + i]);
+      }
+      for (size_t i = 0; r0 + i < r1; ++i) {
+        const int32_t a = rows[r0 + i], nl = S.diag[a] - S.rp[a];
+        const int32_t flags = (a < tb ? kRowFinal : 0) | (S.bus_type[S.blk_bus[a]] == PF_BUS_PV ? kRowPv : 0);
+        rec.insert(rec.end(), {S.blk_bus[a], len(a), off[i % ng], (int32_t)stp.size() / 4});
+        rec.insert(rec.end(), {a, st.pos[S.rp[a]], u_at(a), nl | flags});
+        for (int32_t p = S.rp[a]; p < S.rp[a] + steps(a); ++p) {
+          const int32_t k = S.ci[p], n = S.rp[k + 1] - S.diag[k] - 1;
+          stp.insert(stp.end(), {p - S.rp[a], k, u_at(k), (int32_t)tgt.size()});
+          for (int32_t t = 0; t < n; ++t) tgt.push_back(S.upd_tgt[S.upd_start[p] + t]);
+        }
+      }
+      const int32_t nstep = (int32_t)stp.size() / 4;
+      rec.insert(rec.end(), {0, 0, 0, nstep, 0, 0, 0, 0});
+      stp.insert(stp.end(), {0, 0, 0, (int32_t)tgt.size()});
+      std::vector<int32_t> c = {(int32_t)(r1 - r0), nstep, lg | (std::min(lg_slice, 6 + lg_slice - std::max(lg, 6)) << 8), 0};
+      c.insert(c.end(), rec.begin(), rec.end());
+      c.insert(c.end(), stp.begin(), stp.end());
+      c.insert(c.end(), tgt.begin(), tgt.end());
+      while (c.size() % 4) c.push_back(0);
+      out.ptr.push_back((int32_t)out.blob.size());
+      out.blob.insert(out.blob.end(), c.begin(), c.end());
+      out.max_ints = std::max(out.max_ints, (int32_t)c.size());
+      r0 = r1;
+    }
+  }
+  out.ptr.push_back((int32_t)out.blob.size());
+  return 0;
+}
+
+int build_level_chunks(const Symbolic& S, int32_t budget_ints, LevelChunks& out, std::string& err,
+                       const LuStorage* st_in) {
   out = LevelChunks{};
+  const LuStorage by_position = st_in ? LuStorage{} : storage_by_position(S);
+  const LuStorage& st = st_in ? *st_in : by_position;
   // generic chunker: items of one level are appended to the current chunk
   // while it fits; emit() closes a chunk
   struct Builder {
@@ -69,7 +193,7 @@ int build_level_chunks(const Symbolic& S, int32_t budget_ints, LevelChunks& out,
   };
   const int32_t nb = S.nb, tb = S.tail_base;
   // ---- factor
-  {
+  if (!st.split) {
     Builder B{&out.f_ptr, &out.f_blob};
     for (int32_t h = 0; h < S.n_task_levels; ++h) {
       for (int32_t ti = S.task_ptr[h]; ti < S.task_ptr[h + 1]; ++ti) {
@@ -121,10 +245,10 @@ int build_level_chunks(const Symbolic& S, int32_t budget_ints, LevelChunks& out,
           err = "template: a solve row exceeds the metadata chunk budget";
           return -1;
         }
-        B.rec.insert(B.rec.end(), {a, p0, 0, (int32_t)B.tail.size() / w});
+        B.rec.insert(B.rec.end(), {a, p0 < S.nnzb() ? st.pos[p0] : p0, st.dinv[a], (int32_t)B.tail.size() / w});
         for (int32_t p = p0; p < p1; ++p) {
           B.tail.push_back(S.ci[p]);
-          if (pairs) B.tail.push_back(S.mirror[p]);
+          if (pairs) B.tail.push_back(st.pos[S.mirror[p]]);
         }
         B.n1++;
       }
@@ -145,7 +269,7 @@ int build_level_chunks(const Symbolic& S, int32_t budget_ints, LevelChunks& out,
     const int32_t a = tb + l;
     for (int32_t p = S.rp[a]; p < S.tail_split[l]; ++p) {
       out.tt_pairs.push_back(S.ci[p]);
-      out.tt_pairs.push_back(S.mirror[p]);
+      out.tt_pairs.push_back(st.pos[S.mirror[p]]);
     }
     out.tt_ptr[l + 1] = (int32_t)out.tt_pairs.size() / 2;
   }

@@ -125,7 +125,7 @@ struct Symbolic {
 //           row, first position of the pivot's U row right of the diagonal,
 //           first target}, ntgt row-relative target positions;
 //  solves:  [nrow, ncol, 0, 0], nrow + 1 row records {row, first position,
-//           0, first column}, ncol column indices (forward: the L part of
+//           index of its pivot inverse, first column}, ncol column indices (forward: the L part of
 //           each row, backward: the U part right of the diagonal).
 // The trailing record of each list only carries the end index.
 //  transposed solves (adjoint): as the solves, with a pair (column,
@@ -144,9 +144,53 @@ struct LevelChunks {
   int32_t max_ints = 0;                   // largest chunk, int32 words
 };
 
+// Where the L+U blocks and the inverted pivot blocks of a scenario are stored.
+// By position: block p of the CSR pattern at p, the pivot inverse of row a in
+// an array of its own at a (A = L U, L with unit diagonal).  Split, for the
+// row-by-row factorisation: first the L part and the pivot block of all rows,
+// row after row, then their U parts; the pivot's inverse replaces it, and
+// outside the dense tail U is the unit factor (A = L U with the pivot blocks
+// in L).  A forward solve then streams the first region, a backward solve the
+// second, and an elimination step reads one run of the second.
+struct LuStorage {
+  std::vector<int32_t> pos;    // [nnzb] storage index of each position
+  std::vector<int32_t> dinv;   // [nb] index of each row's pivot inverse
+  bool split = false;
+};
+LuStorage storage_by_position(const Symbolic& S);
+LuStorage storage_split(const Symbolic& S);
+
 // budget_ints: largest chunk in int32 words.  Returns 0, or PF_EINVAL if a
-// single row does not fit the budget.
-int build_level_chunks(const Symbolic& S, int32_t budget_ints, LevelChunks& out, std::string& err);
+// single row does not fit the budget.  st: storage of the blocks (default: by
+// position; the factor tasks are built for that one only, the solves' first
+// positions, transposed positions and tt_pairs follow st).
+int build_level_chunks(const Symbolic& S, int32_t budget_ints, LevelChunks& out, std::string& err,
+                       const LuStorage* st = nullptr);
+
+// Schedule of the row-by-row factorisation (HBM-resident slices, split
+// storage): the rows of each elimination level outside the tail, then the
+// tail rows (which stop before their pivots inside the tail), in chunks as
+// above.  Each row applies all its elimination steps in a buffer in LDS.
+//  [nrow, nstep, log2 lanes per row | log2 scenarios per wavefront << 8, 0],
+//  2 (nrow + 1) row records {bus, blocks, first block of its buffer, first
+//  step} {row, storage of its L part (its pivot block follows), storage of its
+//  U part, L blocks | flags}, nstep + 1 step records {block of the row, pivot
+//  row, storage of the pivot's U part, first target}, targets (blocks of the
+//  row).
+// Rows of a chunk go to the lane groups in turn, longest first; a group's rows
+// share its buffer.
+constexpr int32_t kRowFinal = 1 << 30;   // the row inverts its pivot block (it is outside the tail)
+constexpr int32_t kRowPv = 1 << 29;      // the row's bus is a PV bus
+struct RowChunks {
+  std::vector<int32_t> ptr, blob;
+  int32_t max_ints = 0;
+  int64_t max_buffer = 0;   // largest row buffer area of a chunk, in blocks of one scenario
+};
+// slice scenarios interleaved, threads per workgroup, buffer_blocks: row buffer
+// area in blocks of one scenario.  Returns 0, or PF_EINVAL (err set) when a row
+// fits neither the buffer area nor the chunk budget.
+int build_row_chunks(const Symbolic& S, const LuStorage& st, int32_t slice, int32_t threads,
+                     int64_t buffer_blocks, int32_t budget_ints, RowChunks& out, std::string& err);
 
 // Returns 0 on success; on failure a negative PF_E* code and a message.
 // tail_max: largest dense tail (0 disables it; at most 64)
