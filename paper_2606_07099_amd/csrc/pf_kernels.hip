@@ -1334,7 +1334,7 @@ __device__ __forceinline__ void ltail_fbsolve(const Sym& m, const Dims& D, St<T>
 // tail of scenario w.  Lanes 2l and 2l + 1 hold the two scalar rows of tail
 // block row l (components a b, resp. c d, of every 2x2 block), as register
 // vectors: L part left of the diagonal, the inverted pivot block on it, U
-// part right of it.  The column loops are unrolled over the register
+// part (scaled to unit diagonal after the elimination) right of it.  The column loops are unrolled over the register
 // capacity, so each column is a fixed register and a structurally zero block
 // costs one uniform branch (per-pivot structure masks); only the pivot
 // column is indexed at run time (register-indexing mode, no scratch).  Pivot
@@ -1360,7 +1360,8 @@ constexpr int tail_cap() { return sizeof(T) == 4 ? 32 : 16; }
 template <typename T>
 struct TailRow {
   typedef T V __attribute__((ext_vector_type(tail_cap<T>())));
-  V p, q;   // this lane's scalar row of block j: (p[j], q[j])
+  V p, q;     // this lane's scalar row of block j: (p[j], q[j])
+  T da, db;   // this lane's row of its inverted pivot block: coefficients of its own and of the partner's value
 };
 
 // the partner lane's value (lanes 2l <-> 2l + 1) by a DPP quad permutation
@@ -1425,6 +1426,7 @@ __device__ __forceinline__ void rt_factor(const Sym& m, const Dims& D, St<T>& c,
   // this lane's row of its own pivot block as it was when eliminated, for
   // the pivot test after the loop
   T pvp = T(0), pvq = T(0);
+  T dp = T(0), dq = T(0);   // and its row of the inverse
   // the structure mask of the next pivot is loaded one pivot ahead, so its
   // LDS latency hides behind the current pivot's work
   unsigned mnext = m.tail_mask[0];
@@ -1439,6 +1441,8 @@ __device__ __forceinline__ void rt_factor(const Sym& m, const Dims& D, St<T>& c,
     const T ia = dd * inv, ib = -db * inv, ic = -dc * inv, id = da * inv;
     pvp = l == k ? xp : pvp;
     pvq = l == k ? xq : pvq;
+    dp = l == k ? (h ? ic : ia) : dp;
+    dq = l == k ? (h ? id : ib) : dq;
     const bool below = l > k && l < t;
     // row h of A_lk D_k^-1 on the rows below the pivot, zero elsewhere, so
     // that the update below needs no per-lane select; every lane forms the
@@ -1446,28 +1450,62 @@ __device__ __forceinline__ void rt_factor(const Sym& m, const Dims& D, St<T>& c,
     // register-indexed writes)
     const T m0 = xp * ia + xq * ic, m1 = xp * ib + xq * id;
     const T l0 = below ? m0 : T(0), l1 = below ? m1 : T(0);
-    const T np = below ? m0 : (l == k ? (h ? ic : ia) : xp);
-    const T nq = below ? m1 : (l == k ? (h ? id : ib) : xq);
+    const T np = below ? m0 : (l == k ? dp : xp);
+    const T nq = below ? m1 : (l == k ? dq : xq);
     R.p[k] = np;
     R.q[k] = nq;
     if (fwd) {
       const T yk0 = lane_bcast(y, 2 * k), yk1 = lane_bcast(y, 2 * k + 1);
       y -= l0 * yk0 + l1 * yk1;
     }
-    // eight columns per uniform test, then one test per column
+    if constexpr (sizeof(T) == 4) {
+      // the pivot row's columns one after the other, picked from its mask: a
+      // pivot of a sparse tail has two or three, and testing each of the 32
+      // columns cost more in branches than their arithmetic does
+      // (118-bus x1024 MP launch: tail factorisations 72 us with the tests,
+      // 58 with register-indexed moves)
+      for (unsigned mm = mk; mm; mm &= mm - 1) {
+        const int j = __builtin_ctz(mm);
+        const T rp = R.p[j], rq = R.q[j];
+        const T ua = lane_bcast(rp, 2 * k), ub = lane_bcast(rq, 2 * k);
+        const T uc = lane_bcast(rp, 2 * k + 1), ud = lane_bcast(rq, 2 * k + 1);
+        R.p[j] = rp - (l0 * ua + l1 * uc);
+        R.q[j] = rq - (l0 * ub + l1 * ud);
+      }
+    } else {
+      // 16 columns: eight per uniform test, then one test per column (39 us
+      // against 41 with indexed moves, two per value, on the FP64 launch)
 #pragma unroll
-    for (int jb = 0; jb < tail_cap<T>(); jb += 8) {
-      if ((mk >> jb) & 0xFFu) {
+      for (int jb = 0; jb < tail_cap<T>(); jb += 8) {
+        if ((mk >> jb) & 0xFFu) {
 #pragma unroll
-        for (int j = jb; j < jb + 8; ++j) {
-          if ((mk >> j) & 1u) {
-            const T ua = lane_bcast(R.p[j], 2 * k), ub = lane_bcast(R.q[j], 2 * k);
-            const T uc = lane_bcast(R.p[j], 2 * k + 1), ud = lane_bcast(R.q[j], 2 * k + 1);
-            R.p[j] -= l0 * ua + l1 * uc;
-            R.q[j] -= l0 * ub + l1 * ud;
+          for (int j = jb; j < jb + 8; ++j) {
+            if ((mk >> j) & 1u) {
+              const T ua = lane_bcast(R.p[j], 2 * k), ub = lane_bcast(R.q[j], 2 * k);
+              const T uc = lane_bcast(R.p[j], 2 * k + 1), ud = lane_bcast(R.q[j], 2 * k + 1);
+              R.p[j] -= l0 * ua + l1 * uc;
+              R.q[j] -= l0 * ub + l1 * ud;
+            }
           }
         }
       }
+    }
+  }
+  // U rows scaled by their inverted pivot blocks: the solves then apply the
+  // inverses to all rows at once instead of one after the other in the chain
+  // of the backward substitution (118-bus x1024 MP launch: +7 us here, -3 in
+  // the backward solves and -6 in the refinement's tail solves; the tail of
+  // HBM-resident slices, whose chain waits on LDS, does not gain by it)
+  R.da = h ? dq : dp;
+  R.db = h ? dp : dq;
+  const unsigned cm = __builtin_amdgcn_readfirstlane(m.tail_mask[t + 1]);   // columns with U blocks
+#pragma unroll
+  for (int j = 0; j < tail_cap<T>(); ++j) {
+    if ((cm >> j) & 1u) {
+      const T xp = R.p[j], xq = R.q[j];
+      const T sp = R.da * xp + R.db * pair_swap(xp), sq = R.da * xq + R.db * pair_swap(xq);
+      R.p[j] = l < j ? sp : xp;
+      R.q[j] = l < j ? sq : xq;
     }
   }
   // the pivot test of every block at once (the same arithmetic as at its
@@ -1557,19 +1595,13 @@ __device__ __forceinline__ void rt_bsolve(const Sym& m, const Dims& D, St<T>& c,
     y = c.y[sP<S>(tb + l, s) + h];
     if (dxmode == 2) dxo = c.dx[sP<S>(tb + l, s) + h];
   }
+  y = R.da * y + R.db * pair_swap(y);
   const unsigned cm = __builtin_amdgcn_readfirstlane(m.tail_mask[t + 1]);   // columns with U blocks
 #pragma unroll
   for (int j = tail_cap<T>() - 1; j >= 0; --j) {
-    if (j < t) {
-      const T xp = R.p[j], xq = R.q[j];
-      // x_j = D_j^-1 y_j on the two lanes of row j: row h of the inverse
-      // times both components (the partner lane holds the other one)
-      const T yo = pair_swap(y);
-      if (l == j) y = xp * (h ? yo : y) + xq * (h ? y : yo);
-      if ((cm >> j) & 1u) {
-        const T xj0 = lane_bcast(y, 2 * j), xj1 = lane_bcast(y, 2 * j + 1);
-        if (l < j) y -= xp * xj0 + xq * xj1;
-      }
+    if ((cm >> j) & 1u) {
+      const T xj0 = lane_bcast(y, 2 * j), xj1 = lane_bcast(y, 2 * j + 1);
+      if (l < j) y -= R.p[j] * xj0 + R.q[j] * xj1;
     }
   }
   if (l < t) {
@@ -2166,14 +2198,15 @@ __device__ __forceinline__ void phase_tsolve(const AdjSym& a, const Dims& D, St<
 
 // transposed solves of the tail rows, one wavefront per scenario, lanes 2l
 // and 2l + 1 = the two scalar rows of tail row l: lane row h of block j is
-// column h of the stored block (j, l) (U_jl^T left of the diagonal, the
-// transposed inverted pivot on it, L_jl^T right of it).  U^T forward (after
-// the terms on rows outside the tail), then L^T backward.
+// column h of the stored block (j, l) (U_jl^T left of the diagonal, L_jl^T
+// right of it).  U^T forward (after the terms on rows outside the tail), then
+// L^T backward.  The register tail of LDS-resident slices stores U scaled to
+// unit diagonal (SCALED): the pivot blocks then come in between, all at once.
 // With tl (HBM-resident slices) the tail blocks come from the LDS tail copy
 // (tl, td, located through the tail program's records tq) instead of the
 // slice workspace, and the terms on rows outside the tail from the parts pa
 // (P per row) the whole workgroup summed beforehand.
-template <typename T, int S>
+template <typename T, int S, bool SCALED>
 __device__ __forceinline__ void rt_tsolve(const Sym& m, const AdjSym& a, const Dims& D, St<T>& c, int s, int ln,
                                           const T* tl = nullptr, const T* td = nullptr, const int* tq = nullptr,
                                           const T* pa = nullptr, int P = 0) {
@@ -2190,10 +2223,8 @@ __device__ __forceinline__ void rt_tsolve(const Sym& m, const AdjSym& a, const D
     for (int u = 0; u < 8; ++u) {
       const int j = jb + u;
       p[u] = -1;
-      if (j < t && l < t) {
-        if (j == l) {
-          p[u] = -2;
-        } else if (tl) {
+      if (j < t && l < t && j != l) {
+        if (tl) {
           // compact index of block (j, l): row j's blocks are consecutive
           // in column order, located by its masks
           const int dk = tq[8 * j];
@@ -2212,12 +2243,16 @@ __device__ __forceinline__ void rt_tsolve(const Sym& m, const AdjSym& a, const D
       x0[u] = T(0);
       x1[u] = T(0);
       const T* b = nullptr;
-      if (tl) b = p[u] == -2 ? td + tdB(l, s, t) : (p[u] >= 0 ? tl + tcB(p[u], s, D.tail_nbs) : nullptr);
-      else b = p[u] == -2 ? c.dinv + sB<S>(tb + l, s) : (p[u] >= 0 ? c.lu + sB<S>(p[u], s) : nullptr);
+      if (p[u] >= 0) b = tl ? tl + tcB(p[u], s, D.tail_nbs) : c.lu + sB<S>(p[u], s);
       if (b) { x0[u] = b[h]; x1[u] = b[2 + h]; }
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) { R.p[jb + u] = x0[u]; R.q[jb + u] = x1[u]; }
+  }
+  if (l < t) {   // row h of the transposed inverse of its pivot block
+    const T* b = tl ? td + tdB(l, s, t) : c.dinv + sB<S>(tb + l, s);
+    R.da = b[2 * h + h];
+    R.db = b[2 * (1 - h) + h];
   }
   T y = T(0);
   if (l < t && pa) {
@@ -2252,16 +2287,16 @@ __device__ __forceinline__ void rt_tsolve(const Sym& m, const AdjSym& a, const D
   const unsigned cm = __builtin_amdgcn_readfirstlane(m.tail_mask[t + 1]);
 #pragma unroll
   for (int j = 0; j < C; ++j) {   // U^T w = g
-    if (j < t) {
-      const T xp = R.p[j], xq = R.q[j];
-      const T yo = pair_swap(y);
-      if (l == j) y = xp * (h ? yo : y) + xq * (h ? y : yo);
-      if ((lm >> j) & 1u) {
-        const T w0 = lane_bcast(y, 2 * j), w1 = lane_bcast(y, 2 * j + 1);
-        if (l > j && l < t) y -= xp * w0 + xq * w1;
-      }
+    if (!SCALED && j < t) {
+      const T x = R.da * y + R.db * pair_swap(y);
+      y = l == j ? x : y;
+    }
+    if ((lm >> j) & 1u) {
+      const T w0 = lane_bcast(y, 2 * j), w1 = lane_bcast(y, 2 * j + 1);
+      if (l > j && l < t) y -= R.p[j] * w0 + R.q[j] * w1;
     }
   }
+  if (SCALED) y = R.da * y + R.db * pair_swap(y);
 #pragma unroll
   for (int j = C - 1; j >= 0; --j) {   // L^T lambda = w
     if ((cm >> j) & 1u) {
@@ -2513,11 +2548,11 @@ __global__ void __launch_bounds__(RES ? kResThreads : 1024) k_adjoint_slice(KPar
   auto solve = [&]() {
     phase_tsolve<T, S, RES, true, ROWS>(as, D, c, tid, nt, gmin, stg);
     if constexpr (RES) {
-      for (int s = wv; s < S; s += nw) rt_tsolve<T, S>(m, as, D, c, s, ln);
+      for (int s = wv; s < S; s += nw) rt_tsolve<T, S, true>(m, as, D, c, s, ln);
     } else {
       int P = 0;
       const T* pa = tt_parts<T, S>(as, D, c, tid, nt, stg, P);
-      for (int s = wv; s < S; s += nw) rt_tsolve<T, S>(m, as, D, c, s, ln, tl, td, tq, pa, P);
+      for (int s = wv; s < S; s += nw) rt_tsolve<T, S, false>(m, as, D, c, s, ln, tl, td, tq, pa, P);
     }
     __syncthreads();
     phase_tsolve<T, S, RES, false, ROWS>(as, D, c, tid, nt, gmin, stg);
