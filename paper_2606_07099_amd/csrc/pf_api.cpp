@@ -450,7 +450,8 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
   auto tail_bytes = [&](int sl) { return (size_t)sl * tsz * (4 * tail_nbs + 6 * (size_t)S.tail_t); };
 
   // packs the device image for one storage of the blocks
-  auto pack = [&](const sable::LuStorage& st, const sable::LevelChunks& chunks, const sable::RowChunks* rows) {
+  auto pack = [&](const sable::LuStorage& st, const sable::LevelChunks& chunks, const sable::RowChunks* rows,
+                  const sable::FlowTasks* flow) {
     Packer pk;
     so.bus_type = (int)pk.add(S.bus_type); so.bus_blk = (int)pk.add(S.bus_blk);
     so.y_rp = (int)pk.add(S.y_rp); so.y_ci = (int)pk.add(S.y_ci);
@@ -482,7 +483,11 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
     so.tail_prog = (int)pk.add(prog);
     so.ord_p = (int)pk.add(ord_p); so.ord_q = (int)pk.add(ord_q);
     so.lu_pos = (int)pk.add(st.pos);
-    so.r_ptr = so.r_blob = so.fill_col = so.fill_gb = 0;
+    so.r_ptr = so.r_blob = so.fill_col = so.fill_gb = so.fl_task = so.fl_blob = so.fl_level = 0;
+    if (flow) {
+      so.fl_task = (int)pk.add(flow->task); so.fl_blob = (int)pk.add(flow->blob);
+      so.fl_level = (int)pk.add(flow->per_level);
+    }
     if (rows) {
       std::vector<int32_t> col(S.nnzb());
       std::vector<double> gb(2 * (size_t)S.nnzb(), 0.0);
@@ -527,7 +532,7 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
     sable::LevelChunks chunks;
     const sable::LuStorage st = sable::storage_by_position(S);
     if (sable::build_level_chunks(S, kChunkInts, chunks, err, &st) == 0) {
-      pk = pack(st, chunks, nullptr);
+      pk = pack(st, chunks, nullptr, nullptr);
       for (int sl : {4, 2, 1}) {
         if (sl > sable::kResMaxSlice) continue;
         const size_t need = sable::kScratchBytes + (size_t)so.newton_bytes + sl * per_scen;
@@ -571,6 +576,7 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
     while (sl < sable::kMaxSlice && batch / (2 * sl) >= n_cu) sl *= 2;
     sable::LevelChunks chunks;
     sable::RowChunks rows;
+    sable::FlowTasks flow;
     const size_t fixed = sable::kScratchBytes + prefix_bytes;
     size_t y_bytes = 0, area = 0;
     int32_t budget = 0;
@@ -596,20 +602,36 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
       if (by_rows) {
         dm.chunk_ints = std::max(dm.chunk_ints, budget);
         area = max_lds - fixed - y_bytes - 4 * (size_t)dm.chunk_ints;
-        r = sable::build_row_chunks(S, st, sl, nt, (int64_t)(area / (4 * tsz * sl)), budget, rows, err);
+        dm.n_flow = dm.flow_levels = 0;
+        rows = sable::RowChunks{};
+        flow = sable::FlowTasks{};
+        if (sl == 1) {
+          // wavefront tasks, each wavefront with its share of the buffers and
+          // of the metadata area, behind which the levels are counted
+          const int waves = nt / 64, counts = (S.n_fs_levels + 2 + 3) / 4 * 4;
+          dm.flow_buf = (int)(area / (4 * tsz)) / waves;
+          dm.flow_meta = std::min<int>(sable::kFlowMaxWords, std::max(0, dm.chunk_ints - counts) / waves / 4 * 4);
+          r = sable::build_flow_tasks(S, st, waves, dm.flow_buf, dm.flow_meta, flow, err);
+          dm.n_flow = flow.n_tasks();
+          dm.flow_levels = (int)flow.per_level.size();
+        } else {
+          r = sable::build_row_chunks(S, st, sl, nt, (int64_t)(area / (4 * tsz * sl)), budget, rows, err);
+        }
         if (r != 0) return r;
       } else {
         area = tail_bytes(sl);
       }
-      pk = pack(st, chunks, by_rows ? &rows : nullptr);
+      pk = pack(st, chunks, by_rows ? &rows : nullptr, by_rows ? &flow : nullptr);
       return 0;
     };
-    // Slices of one scenario factor by levels: there the chain of a row's
-    // steps, not the traffic, sets the time (1354-bus grid, 37 scenarios, FP64
-    // layer: 1.04 ms by levels, 1.25 by rows; 9241-bus grid, mixed: 9.4 and
-    // 10.1 ms), while 16 scenarios per slice gain 1.1 to 1.5 times.
+    // Slices of one scenario with FP32 factors factor by levels in place on the
+    // smaller grids: there a levelled pass costs little more than its barrier
+    // (1354 buses x250, mixed: 1.55 ms by levels, 1.65 by rows; FP64 0.97 both;
+    // 300 buses x250, FP64: 0.36 and 0.34; 9241 buses x256, mixed: 9.4 and 8.8,
+    // FP64 9.6 and 6.5).
     t->rows = true;
-    while ((rc = sl > 1 ? plan(true) : PF_EINVAL) != 0 && sl > 1) sl /= 2;
+    const bool by_levels = t->fp32 && S.nb < 4096;
+    while ((rc = sl == 1 && by_levels ? PF_EINVAL : plan(true)) != 0 && sl > 1) sl /= 2;
     if (rc != 0) {
       t->rows = false;
       sl = 1;

@@ -67,6 +67,7 @@ struct SymOffsets {
   int rp, ci, diag, fill4, tail_pos, tail_split, tail_mask;
   int f_ptr, f_blob, fs_ptr, fs_blob, bs_ptr, bs_blob;   // level metadata chunks
   int r_ptr, r_blob, fill_col, fill_gb;   // row-by-row factorisation: chunks; per stored block column bus | flags, Y entry
+  int fl_task, fl_blob, fl_level;         // its wavefront tasks: entries, records, tasks per level
   int newton_bytes;
   // [newton_bytes, adj_bytes): what the LDS-resident adjoint reads besides
   int ut_ptr, ut_blob, lt_ptr, lt_blob, tt_ptr, tt_pairs, y_tr;
@@ -85,6 +86,9 @@ struct Dims {
   int tail_t, tail_base;          // dense tail rows [tail_base, tail_base + tail_t)
   int nch_f, nch_fs, nch_bs;      // metadata chunks of the factor, forward and backward levels
   int nch_r;                      // metadata chunks of the row-by-row factorisation
+  int n_flow, flow_levels;        // its wavefront tasks and their levels (0: chunks only)
+  int flow_meta;                  // words of a wavefront's task record area
+  int flow_buf;                   // row buffer of a wavefront, in blocks of one scenario
   int nch_ut, nch_lt;             // metadata chunks of the transposed solves
   int chunk_ints;                 // largest chunk (int32 words), staged after the LDS scratch
   int tail_nblk;                  // blocks of the tail rows in tail columns (LDS tail copy)

@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <complex>
+#include <cstring>
 #include <numeric>
 #include <queue>
 
@@ -158,6 +159,81 @@ int build_row_chunks(const Symbolic& S, const LuStorage& st, int32_t slice, int3
     }
   }
   out.ptr.push_back((int32_t)out.blob.size());
+  return 0;
+}
+
+int build_flow_tasks(const Symbolic& S, const LuStorage& st, int32_t waves, int64_t buffer_blocks,
+                     int32_t budget_ints, FlowTasks& out, std::string& err) {
+  out = FlowTasks{};
+  std::vector<int32_t> level(S.nb, 0);
+  const int32_t nlev = S.n_fs_levels, tb = S.tail_base;   // levels outside the tail
+  if (nlev + 1 > kFlowMaxLevels) { err = "template: too many levels to count"; return PF_EINVAL; }
+  for (int32_t h = 0; h < nlev; ++h)
+    for (int32_t q = S.lev_l_ptr[h]; q < S.lev_l_ptr[h + 1]; ++q) level[S.lev_l_rows[q]] = h;
+  auto len = [&](int32_t a) { return S.rp[a + 1] - S.rp[a]; };
+  auto n_u = [&](int32_t a) { return S.rp[a + 1] - S.diag[a] - 1; };
+  auto steps = [&](int32_t a) { return (a < tb ? S.diag[a] : S.tail_split[a - tb]) - S.rp[a]; };
+  auto u_at = [&](int32_t a) { return n_u(a) > 0 ? st.pos[S.diag[a] + 1] : 0; };
+  for (int32_t h = 0; h < nlev + (tb < S.nb ? 1 : 0); ++h) {
+    std::vector<int32_t> rows;
+    if (h < nlev) rows.assign(S.lev_l_rows.begin() + S.lev_l_ptr[h], S.lev_l_rows.begin() + S.lev_l_ptr[h + 1]);
+    else for (int32_t a = tb; a < S.nb; ++a) rows.push_back(a);
+    std::stable_sort(rows.begin(), rows.end(), [&](int32_t x, int32_t y) { return len(x) > len(y); });
+    int32_t tasks = 0;
+    for (size_t r0 = 0; r0 < rows.size();) {
+      const int32_t longest = len(rows[r0]);
+      if (longest > kFlowMaxRow) { err = "template: a row is too long for one-byte targets"; return PF_EINVAL; }
+      // sixteen rows of four lanes; fewer and wider ones while they do not fit
+      // the buffer or the level makes fewer tasks than a quarter of the
+      // wavefronts (levels overlap, so a level need not occupy all of them)
+      int32_t m = 16, lg = 2;
+      while (m > 1 && ((int64_t)(rows.size() + m - 1) / m * 4 < waves || (int64_t)m * longest > buffer_blocks)) {
+        m /= 2;
+        ++lg;
+      }
+      if (longest > buffer_blocks) { err = "template: a row of the factorisation exceeds the row buffers"; return PF_EINVAL; }
+      size_t r1 = std::min(rows.size(), r0 + m);
+      auto words = [&] {
+        int64_t w = 4, tg = 0;
+        for (size_t i = r0; i < r1; ++i) {
+          const int32_t a = rows[i];
+          w += 8 + 4 * steps(a);
+          for (int32_t p = S.rp[a]; p < S.rp[a] + steps(a); ++p) tg += n_u(S.ci[p]);
+        }
+        return w + (tg + 15) / 16 * 4;
+      };
+      while (r1 > r0 + 1 && words() > budget_ints) --r1;
+      if (words() > budget_ints) { err = "template: a row of the factorisation exceeds its metadata"; return PF_EINVAL; }
+      std::vector<int32_t> rec, stp;
+      std::vector<unsigned char> tgt;
+      int32_t off = 0, most = 0;
+      for (size_t i = r0; i < r1; ++i) {
+        const int32_t a = rows[i], nl = S.diag[a] - S.rp[a];
+        const int32_t flags = (a < tb ? kRowFinal : 0) | (S.bus_type[S.blk_bus[a]] == PF_BUS_PV ? kRowPv : 0);
+        rec.insert(rec.end(), {S.blk_bus[a], len(a) | (steps(a) << 16), off, (int32_t)stp.size() / 4});
+        rec.insert(rec.end(), {a, st.pos[S.rp[a]], u_at(a), nl | flags});
+        for (int32_t p = S.rp[a]; p < S.rp[a] + steps(a); ++p) {
+          const int32_t k = S.ci[p];
+          stp.insert(stp.end(), {(p - S.rp[a]) | (n_u(k) << 8) | (level[k] << 16), k, u_at(k), (int32_t)tgt.size()});
+          for (int32_t t = 0; t < n_u(k); ++t) tgt.push_back((unsigned char)S.upd_tgt[S.upd_start[p] + t]);
+        }
+        off += len(a);
+        most = std::max(most, steps(a));
+      }
+      std::vector<int32_t> c = {(int32_t)(r1 - r0), lg, h, most};
+      c.insert(c.end(), rec.begin(), rec.end());
+      c.insert(c.end(), stp.begin(), stp.end());
+      const size_t at = c.size();
+      c.resize(at + (tgt.size() + 15) / 16 * 4, 0);
+      if (!tgt.empty()) std::memcpy(c.data() + at, tgt.data(), tgt.size());
+      out.task.insert(out.task.end(), {(int32_t)out.blob.size(), (int32_t)c.size() / 4});
+      out.blob.insert(out.blob.end(), c.begin(), c.end());
+      out.max_ints = std::max(out.max_ints, (int32_t)c.size());
+      ++tasks;
+      r0 = r1;
+    }
+    out.per_level.push_back(tasks);
+  }
   return 0;
 }
 

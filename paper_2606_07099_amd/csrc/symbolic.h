@@ -192,6 +192,31 @@ struct RowChunks {
 int build_row_chunks(const Symbolic& S, const LuStorage& st, int32_t slice, int32_t threads,
                      int64_t buffer_blocks, int32_t budget_ints, RowChunks& out, std::string& err);
 
+// The same rows as tasks of single wavefronts (slices of one scenario), in level
+// order, the tail rows as a last level: a wavefront takes the next task, and
+// before a step waits until the level of the step's pivot is done (all tasks of
+// that level finished).  A task only waits for tasks before it.  Its record:
+//  [rows, log2 lanes per row, level, most steps of a row], 2 rows records {bus,
+//  blocks | steps << 16, first block of its buffer, first step} {row, storage of
+//  its L part, storage of its U part, L blocks | flags}, step records {block of
+//  the row | U blocks << 8 | level of the pivot << 16, pivot row, storage of the
+//  pivot's U part, first target}, targets (blocks of the row, one byte each).
+constexpr int32_t kFlowMaxRow = 255;       // blocks of a row (one-byte targets)
+constexpr int32_t kFlowMaxLevels = 1024;   // levels counted in LDS
+constexpr int32_t kFlowMaxWords = 768;     // words of a record (three 16-byte loads per lane)
+struct FlowTasks {
+  std::vector<int32_t> task;      // [tasks][2]: first word of its record, 16-byte words of it
+  std::vector<int32_t> blob;      // the records
+  std::vector<int32_t> per_level; // [levels] tasks
+  int32_t max_ints = 0;           // longest record
+  int32_t n_tasks() const { return (int32_t)task.size() / 2; }
+};
+// waves: wavefronts of the workgroup; buffer_blocks: row buffer of a wavefront;
+// budget_ints: record words of a wavefront.  Returns 0, or PF_EINVAL (err set)
+// when a row or the levels do not fit.
+int build_flow_tasks(const Symbolic& S, const LuStorage& st, int32_t waves, int64_t buffer_blocks,
+                     int32_t budget_ints, FlowTasks& out, std::string& err);
+
 // Returns 0 on success; on failure a negative PF_E* code and a message.
 // tail_max: largest dense tail (0 disables it; at most 64)
 int analyze(int32_t n_bus, const int32_t* bus_type, const int32_t* y_indptr,

@@ -8,6 +8,10 @@
 // tail, and the tail rows' partial sums, equal a plain block LU of the pattern
 // to 1e-9 (random diagonally dominant values); the solve schedules' first
 // positions, pivot inverses and transposed positions follow the storage.
+// The wavefront tasks of the same rows are replayed after it: tasks in level
+// order, each step's pivot of a lower level that its record names, every row
+// once, buffers and records within a wavefront's share, and the
+// same factors.
 // Usage: rows_check NET TAIL_MAX SLICE THREADS BUFFER_BLOCKS BUDGET
 #include <algorithm>
 #include <array>
@@ -155,6 +159,78 @@ int main(int argc, char** argv) {
     }
   }
   CHECK(worst < 1e-9, "factors differ by %g", worst);
+
+  // ---- wavefront tasks, with a sixteenth of the areas each
+  const int waves = threads / 64;
+  const int64_t share = area * slice / waves;
+  const int meta = std::min(kFlowMaxWords, budget / waves / 4 * 4);
+  FlowTasks F;
+  if (build_flow_tasks(S, st, waves, share, meta, F, err) != 0) {
+    std::printf("flow refused: %s\n", err.c_str());
+  } else {
+    std::vector<B> fl(nz);
+    std::vector<int> lev(nb, -1), cover(nb, 0), count(F.per_level.size(), 0);
+    int last = 0;
+    CHECK(F.max_ints <= meta, "task record of %d words", F.max_ints);
+    for (int k = 0; k < F.n_tasks(); ++k) {
+      const int32_t* c = &F.blob[F.task[2 * k]];
+      const int words = F.task[2 * k + 1];
+      const int nrow = c[0], lanes = 1 << c[1], h = c[2], most = c[3];
+      CHECK(F.task[2 * k] % 4 == 0 && F.task[2 * k] + 4 * words <= (int)F.blob.size(), "task %d record", k);
+      CHECK(h >= last && h < (int)F.per_level.size(), "task %d of level %d after %d", k, h, last);
+      CHECK(lanes <= 64 && nrow >= 1 && nrow * lanes <= 64, "task %d geometry", k);
+      last = h;
+      count[h]++;
+      const int32_t* sp = c + 4 + 8 * nrow;
+      const int32_t* lr = c + 4 + 8 * (nrow - 1);
+      const int nsteps = lr[3] + (lr[1] >> 16);
+      const unsigned char* tg = reinterpret_cast<const unsigned char*>(sp + 4 * nsteps);
+      int blocks = 0, longest = 0;
+      for (int i = 0; i < nrow; ++i) {
+        const int32_t *r0 = c + 4 + 8 * i, *r1 = r0 + 4;
+        const int a = r1[0], n = r0[1] & 0xffff, ns = r0[1] >> 16, nl = r1[3] & (kRowPv - 1);
+        int outer = 0;
+        for (int p = S.rp[a]; p < S.diag[a]; ++p) outer += S.ci[p] < tb;
+        CHECK(a >= 0 && a < nb && r0[0] == S.blk_bus[a] && n == S.rp[a + 1] - S.rp[a] && ns == outer && nl == S.diag[a] - S.rp[a], "task row %d", a);
+        CHECK(((r1[3] & kRowFinal) != 0) == (a < tb), "task row %d: final", a);
+        CHECK(((r1[3] & kRowPv) != 0) == (bt[S.blk_bus[a]] == PF_BUS_PV), "task row %d flags", a);
+        CHECK(r0[2] == blocks, "task row %d buffer", a);
+        blocks += n;
+        longest = std::max(longest, ns);
+        cover[a]++;
+        lev[a] = h;
+        for (int j = 0; j < n; ++j) CHECK((j <= nl ? r1[1] + j : r1[2] + j - nl - 1) == st.pos[S.rp[a] + j], "task row %d block %d", a, j);
+        std::vector<B> W(n);
+        for (int j = 0; j < n; ++j) W[j] = A[S.rp[a] + j];
+        for (int q = 0; q < ns; ++q) {
+          const int32_t* x = sp + 4 * (r0[3] + q);
+          const int piv = x[1], nu = (x[0] >> 8) & 255, blk = x[0] & 255;
+          CHECK(blk == q && piv == S.ci[S.rp[a] + q] && nu == S.rp[piv + 1] - S.diag[piv] - 1 && nu >= 1, "task row %d step %d", a, q);
+          CHECK(lev[piv] >= 0 && lev[piv] < h && (x[0] >> 16) == lev[piv], "task row %d: level of pivot %d", a, piv);
+          CHECK(x[2] == st.pos[S.diag[piv] + 1], "task row %d: pivot row", a);
+          for (int j = 0; j < nu; ++j) {
+            const int w = tg[x[3] + j];
+            CHECK(x[3] + j < 4 * (4 * words - (int)(sp + 4 * nsteps - c)) && w > blk && w < n, "task row %d target", a);
+            CHECK(S.ci[S.rp[a] + w] == S.ci[S.diag[piv] + 1 + j], "task row %d step %d target %d", a, q, j);
+            W[w] = sub(W[w], mul(W[blk], fl[x[2] + j]));
+          }
+        }
+        if (a < tb) {
+          W[nl] = inv(W[nl]);
+          for (int j = nl + 1; j < n; ++j) W[j] = mul(W[nl], W[j]);
+        }
+        for (int j = 0; j < n; ++j) fl[st.pos[S.rp[a] + j]] = W[j];
+      }
+      CHECK(blocks <= share && longest == most, "task %d: buffer of %d blocks, %d steps", k, blocks, most);
+    }
+    for (size_t h = 0; h < count.size(); ++h) CHECK(count[h] == F.per_level[h], "level %zu: %d tasks", h, count[h]);
+    for (int a = 0; a < nb; ++a) {
+      CHECK(cover[a] == 1, "row %d in %d tasks", a, cover[a]);
+      for (int p = S.rp[a]; p < S.rp[a + 1]; ++p)
+        for (int c = 0; c < 4; ++c) CHECK(fl[st.pos[p]][c] == lu[st.pos[p]][c], "row %d: task values", a);
+    }
+    std::printf("flow tasks %d words %d ", F.n_tasks(), F.max_ints);
+  }
 
   LevelChunks C;
   if (build_level_chunks(S, budget, C, err, &st) != 0) return 3;
