@@ -403,7 +403,12 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
   // the dense tail of an LDS-resident slice lives in registers: at most 32
   // block rows in FP32, 16 in FP64
   const int tail_max = opt.precision == PF_MIXED ? 32 : 16;
-  int rc = sable::analyze(n_bus, bus_type, y_indptr, y_indices, y_g, y_b, t->sym, err, tail_max);
+  // and an FP64 tail takes in levels of at most four rows: a row costs the tail
+  // 0.7 us per factorisation, a level outside it 2.6 us per update (factor and
+  // backward pass), which the tail's wavefront alone no longer beats.  With FP32
+  // factors a level also costs the refinement's four solves, a tail row less.
+  const int tail_level = opt.precision == PF_MIXED ? tail_max : 4;
+  int rc = sable::analyze(n_bus, bus_type, y_indptr, y_indices, y_g, y_b, t->sym, err, tail_max, tail_level);
   if (rc != PF_OK) { delete t; return fail(rc, err); }
   if (!structurally_symmetric(t->sym)) {
     delete t;

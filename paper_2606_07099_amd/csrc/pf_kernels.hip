@@ -1066,6 +1066,8 @@ __device__ __forceinline__ void phase_solve(const Sym& m, const Dims& D, St<T>& 
   for (int ch = 0; ch < nch; ++ch) {
     const int* h = stg.get(ch);
     const int nrow = h[0];
+    // a forward level without entries leaves its right-hand sides as they are
+    if (RES && LOWER && !UNITU && __builtin_amdgcn_readfirstlane(h[1]) == 0) continue;
     const int4* rw = reinterpret_cast<const int4*>(h + 4);
     const int* cols = reinterpret_cast<const int*>(rw + nrow + 1);
     const Grp g = groups(nrow, tid, nt, gmin);

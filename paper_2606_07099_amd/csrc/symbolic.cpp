@@ -405,7 +405,7 @@ int ybus_from_branches(int32_t n_bus, int32_t n_branch, const int32_t* f, const 
 
 int analyze(int32_t n_bus, const int32_t* bus_type, const int32_t* y_indptr,
             const int32_t* y_indices, const double* y_g, const double* y_b, Symbolic& S,
-            std::string& err, int32_t tail_max) {
+            std::string& err, int32_t tail_max, int32_t tail_level) {
   if (n_bus < 2 || !bus_type || !y_indptr || !y_indices || !y_g || !y_b) {
     err = "template: need n_bus >= 2 and non-null bus_type / Y_bus arrays";
     return PF_EINVAL;
@@ -630,7 +630,10 @@ int analyze(int32_t n_bus, const int32_t* bus_type, const int32_t* y_indptr,
     std::vector<int32_t> cnt(nl + 1, 0);
     for (int32_t a = 0; a < nb; ++a) cnt[lev_l[a]]++;
     int32_t h = nl, t = 0;
-    while (h > 0 && t + cnt[h - 1] <= std::min<int32_t>(tail_max, 64)) { t += cnt[h - 1]; --h; }
+    while (h > 0 && t + cnt[h - 1] <= std::min<int32_t>(tail_max, 64) && cnt[h - 1] <= tail_level) {
+      t += cnt[h - 1];
+      --h;
+    }
     if (t < 4) { t = 0; h = nl; }
     S.tail_t = t;
     S.tail_h = h;

@@ -218,10 +218,11 @@ int build_flow_tasks(const Symbolic& S, const LuStorage& st, int32_t waves, int6
                      int32_t budget_ints, FlowTasks& out, std::string& err);
 
 // Returns 0 on success; on failure a negative PF_E* code and a message.
-// tail_max: largest dense tail (0 disables it; at most 64)
+// tail_max: largest dense tail (0 disables it; at most 64); tail_level: most
+// rows of a level that the tail takes in
 int analyze(int32_t n_bus, const int32_t* bus_type, const int32_t* y_indptr,
             const int32_t* y_indices, const double* y_g, const double* y_b,
-            Symbolic& out, std::string& err, int32_t tail_max = 32);
+            Symbolic& out, std::string& err, int32_t tail_max = 32, int32_t tail_level = 64);
 
 // pi-model branch admittances assembled into CSR (columns sorted, duplicate
 // branches summed).  Returns nnz, or a negative error code.
