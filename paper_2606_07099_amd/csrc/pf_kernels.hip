@@ -570,7 +570,8 @@ __device__ __forceinline__ void phase_fill(const Sym& m, const Dims& D, St<T>& c
   constexpr int NB = RES ? 4 : 2;
   // NB blocks per thread have their gathers in flight together
   const int N = D.nnzb * S;
-  for (int base = tid; base < N; base += NB * nt) {
+  int base = tid;
+  for (; RES ? base + (NB - 1) * nt < N : base < N; base += NB * nt) {
     FillIn q[NB];
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
@@ -584,6 +585,14 @@ __device__ __forceinline__ void phase_fill(const Sym& m, const Dims& D, St<T>& c
       const int idx = base + u * nt;
       if (idx < N) st_blk(c.lu + sB<S>(idx / S, idx % S), fill_value<T, RES>(q[u]));
     }
+  }
+  // LDS-resident slices take the last blocks one by one: a round of four is
+  // four blocks' instructions, also where only one of them exists
+  for (; RES && base < N; base += nt) {
+    FillIn q;
+    q.r = m.fill4[base / S];
+    fill_gather<T, S, RES>(m, c, base % S, q);
+    st_blk(c.lu + sB<S>(base / S, base % S), fill_value<T, RES>(q));
   }
   __syncthreads();
 }
