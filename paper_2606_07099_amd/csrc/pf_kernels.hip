@@ -2257,8 +2257,8 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
         if (b >= kp.count) break;
         double* gd = kp.ws_d + (size_t)b * kp.lay.sd;
         T* gt = reinterpret_cast<T*>(kp.ws_t) + (size_t)b * kp.lay.st;
-        for (int q = tid; q < 4 * D.nnzb; q += nt) gt[kp.lay.o_lu + q] = c.lu[sB<S>(q >> 2, s) + (q & 3)];
-        for (int q = tid; q < 4 * nb; q += nt) gt[kp.lay.o_dinv + q] = c.dinv[sB<S>(q >> 2, s) + (q & 3)];
+        for (int q = tid; q < D.nnzb; q += nt) st_blk(gt + kp.lay.o_lu + 4 * q, ld_blk(c.lu + sB<S>(q, s)));
+        for (int q = tid; q < nb; q += nt) st_blk(gt + kp.lay.o_dinv + 4 * q, ld_blk(c.dinv + sB<S>(q, s)));
         for (int i = tid; i < n; i += nt) {
           const int gi = i * kp.lay.gk;   // the per-scenario workspace groups them
           gd[kp.lay.o_e + gi] = c.e[c.g(i, s)];
@@ -2665,17 +2665,15 @@ __global__ void __launch_bounds__(RES ? kResThreads : 1024) k_adjoint_slice(KPar
     c.f[c.g(i, s)] = f;
     c.vm[c.g(i, s)] = v;
   }
-  for (int q = tid; q < 4 * D.nnzb * S; q += nt) {
-    const int comp = q & 3, blk = q >> 2, p = blk / S, s = blk % S;
-    const int b = slice * S + s;
-    c.lu[q] = b < kp.count ? reinterpret_cast<const T*>(kp.ws_t)[(size_t)b * kp.lay.st + kp.lay.o_lu + 4 * p + comp]
-                           : T(0);
+  for (int q = tid; q < D.nnzb * S; q += nt) {
+    const int b = slice * S + q % S;
+    const T* g = reinterpret_cast<const T*>(kp.ws_t) + (size_t)b * kp.lay.st + kp.lay.o_lu + 4 * (q / S);
+    st_blk(c.lu + 4 * q, b < kp.count ? ld_blk(g) : Blk<T>{T(0), T(0), T(0), T(0)});
   }
-  for (int q = tid; q < 4 * nb * S; q += nt) {
-    const int comp = q & 3, blk = q >> 2, p = blk / S, s = blk % S;
-    const int b = slice * S + s;
-    c.dinv[q] = b < kp.count ? reinterpret_cast<const T*>(kp.ws_t)[(size_t)b * kp.lay.st + kp.lay.o_dinv + 4 * p + comp]
-                             : ((comp == 0 || comp == 3) ? T(1) : T(0));
+  for (int q = tid; q < nb * S; q += nt) {
+    const int b = slice * S + q % S;
+    const T* g = reinterpret_cast<const T*>(kp.ws_t) + (size_t)b * kp.lay.st + kp.lay.o_dinv + 4 * (q / S);
+    st_blk(c.dinv + 4 * q, b < kp.count ? ld_blk(g) : Blk<T>{T(1), T(0), T(0), T(1)});
   }
   }
   // HBM-resident slices: the factored tail in LDS, as the Newton kernel
