@@ -75,17 +75,15 @@ class SyntheticDispatchTask:
         self.u = torch.as_tensor(u, dtype=torch.float32, device=dev)
         self.model = DispatchMLP(u.shape[1], int(self.pv.numel()), int(self.gen.numel()),
                                  hidden).to(dev)
-        # one launch per optimizer step: the default per-operation form issues over a
-        # dozen, and the host's launches bound a training step of this size
-        self.opt = torch.optim.Adam(self.model.parameters(), lr=lr, fused=True)
-        self.zeros = torch.zeros_like(self.pg0)
+        self.opt = torch.optim.Adam(self.model.parameters(), lr=lr)
         self.c2, self.c1 = cost
         self.v_weight, self.q_weight = v_weight, q_weight
 
     def forward_loss(self):
         dp, dv = self.model(self.u)
-        pg = self.pg0 * (1.0 + self.zeros.index_add(1, self.pv, dp.double()))
-        vset = self.vset0 + self.zeros.index_add(1, self.gen, dv.double())
+        zeros = torch.zeros_like(self.pg0)
+        pg = self.pg0 * (1.0 + zeros.index_add(1, self.pv, dp.double()))
+        vset = self.vset0 + zeros.index_add(1, self.gen, dv.double())
         vm, va, po, qo = self.layer(self.pd, self.qd, pg, vset)
         # every generator's active output: x's dispatch on PV buses and the
         # recovered p_g on the slack bus (pg_out holds both)
