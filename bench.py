@@ -52,15 +52,15 @@ KERNEL_SOURCES = ("paper_2606_07099_amd/csrc/pf_kernels.hip", "paper_2606_07099_
 # the kernel sources they were taken on; a changed kernel reports null.
 # Sources: profiles/*_hbm_counters.md
 MEASURED_TRAFFIC = {
-    "0e9949f99c6bfeb39010a3811daa701dedba881ec271c092c0951986c17ab1d1": {
-        "c1/mixed": 7003853,
-        "c1/fp64": 6899376,
-        "c2/mixed": 43249094750,
-        "c2/fp64": 46121311935,
-        "c3/mixed": 2992607351,
-        "c3/fp64": 3339025927,
-        "c4/mixed": 37813363924,
-        "c4/fp64": 39909501093,
+    "e7090cbcd346056ea15b8c988819d2a38513d591362b3b0d3f41dd58bcc91f96": {
+        "c1/mixed": 6967990,
+        "c1/fp64": 6901440,
+        "c2/mixed": 35279100000,
+        "c2/fp64": 27374300000,
+        "c3/mixed": 2524166000,
+        "c3/fp64": 2008802000,
+        "c4/mixed": 31073140000,
+        "c4/fp64": 29438650000,
     },
 }
 

@@ -24,8 +24,9 @@ enum Mode : int {
 enum PhaseSlot : int {
   PH_SETUP = 0,                // inputs, flat start
   PH_MISMATCH = 1,             // I = Y V, F1, norms and the convergence test
-  PH_FILL = 2,                 // Jacobian values into the LU positions (Algorithm 1)
-  PH_FACTOR_LEVELS = 3,        // level-scheduled factorisation with the fused forward solve
+  PH_FILL = 2,                 // Jacobian values into the LU positions (Algorithm 1); part of the next where rows are
+                               // formed in the factorisation
+  PH_FACTOR_LEVELS = 3,        // factorisation outside the tail with the fused forward solve
   PH_FACTOR_TAIL = 4,          // dense tail factorisation (+ its forward solve)
   PH_BSOLVE_TAIL = 5,          // backward solve of the tail rows
   PH_BSOLVE_LEVELS = 6,        // level-scheduled backward solve

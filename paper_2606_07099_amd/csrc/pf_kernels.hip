@@ -1,22 +1,26 @@
 // Device kernels of the batched Newton power flow for CDNA4 (gfx950).
 //
-// One workgroup owns a slice of S scenarios (S = 1, 2, 4 or 8) for the whole
-// Newton solve, with no host round trip per iteration: complex Y_bus SpMV +
-// mismatch, per-scenario convergence test, Jacobian value evaluation
-// (Algorithm 1) into the fixed symbolic pattern, a 2x2-block LU
-// refactorisation scheduled right-looking by levels (forward solve fused),
-// the level-scheduled backward solve, FP64-residual refinement in the
-// mixed-precision mode, and the state update.  Converged scenarios of a slice
-// freeze while the others continue.
+// One workgroup owns a slice of S scenarios (1, 2 or 4, HBM-resident up to 16)
+// for the whole Newton solve, with no host round trip per iteration: complex
+// Y_bus SpMV + mismatch, per-scenario convergence test, Jacobian value
+// evaluation (Algorithm 1) into the fixed symbolic pattern, a 2x2-block LU
+// refactorisation (forward solve fused), the level-scheduled backward solve,
+// FP64-residual refinement in the mixed-precision mode, and the state update.
+// Converged scenarios of a slice freeze while the others continue.
 //
 // Two residency modes:
 //  * LDS-resident (small grids): the symbolic image and the whole state of
 //    the S scenarios live in LDS; arrays are interleaved by scenario, so a
 //    lane's scenario index is its lane index modulo S and the S lanes that
-//    share an index load or update adjacent LDS words.
-//  * HBM-resident (large grids, S = 1): the state lives in the scenario's
-//    HBM workspace, the symbolic arrays are read from the shared image (L2),
-//    and only the factor row under elimination is staged in LDS.
+//    share an index load or update adjacent LDS words.  Right-looking LU by
+//    levels after a pass of Jacobian values.
+//  * HBM-resident (larger grids): the state lives in the slice's HBM
+//    workspace, interleaved the same way, the symbolic arrays are read from the
+//    shared image (L2).  Up-looking LU, each row formed and eliminated in LDS:
+//    by levels with a barrier each (several scenarios), or as wavefront tasks
+//    that wait for each other's rows (one scenario).  Slices of one scenario
+//    whose rows do not fit, or with FP32 factors on smaller grids, factor by
+//    levels in place.
 #include "pf_kernels.h"
 
 #include <hip/hip_runtime.h>
