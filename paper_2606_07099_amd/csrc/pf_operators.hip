@@ -15,6 +15,7 @@
 namespace sable {
 
 __global__ void __launch_bounds__(256) k_operator_state(OpParams p) {
+#pragma clang fp contract(off)
   const size_t o = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (o >= (size_t)p.count * p.n_bus) return;
   const size_t row = o - o % p.n_bus;
@@ -28,14 +29,14 @@ __global__ void __launch_bounds__(256) k_operator_state(OpParams p) {
     double sk, ck;
     sincos(p.va[c], &sk, &ck);
     const double ek = p.vm[c] * ck, fk = p.vm[c] * sk;
-    ir += p.y_g[k] * ek - p.y_b[k] * fk;
-    ii += p.y_g[k] * fk + p.y_b[k] * ek;
+    ir += fma(p.y_g[k], ek, -(p.y_b[k] * fk));
+    ii += fma(p.y_g[k], fk, p.y_b[k] * ek);
   }
   double4 w;
   w.x = e;
   w.y = f;
-  w.z = e * ir + f * ii;   // P_i
-  w.w = f * ir - e * ii;   // Q_i
+  w.z = fma(f, ii, e * ir);      // P_i
+  w.w = fma(f, ir, -(e * ii));   // Q_i
   reinterpret_cast<double4*>(p.ef)[o] = w;
 }
 
@@ -49,32 +50,25 @@ __global__ void __launch_bounds__(256) k_operator_state(OpParams p) {
 //   on the diagonal, with the row's own P_i and Q_i,
 //     dP_i/dtheta_i = -Q_i - B_ii |V_i|^2, dP_i/d|V|_i = P_i / |V|_i + G_ii |V|_i,
 //     dQ_i/dtheta_i = P_i - G_ii |V_i|^2,  dQ_i/d|V|_i = Q_i / |V|_i - B_ii |V|_i.
-// one value of one scenario
-__device__ __forceinline__ double entry_value(const OpParams& p, int kind, int i, int j, double G, double Bv,
-                                              size_t b) {
-  const double* vm = p.vm + b * p.n_bus;
-  const double4* st = reinterpret_cast<const double4*>(p.ef) + b * p.n_bus;
-  const double4 si = st[i];
-  const double ei = si.x, fi = si.y;
-  double dp, dq;   // derivatives of P_i and Q_i
-  const bool dva = kind == BK_DP_DVA || kind == BK_DQ_DVA;
-  if (i != j) {
-    const double4 sj = st[j];
-    const double ej = sj.x, fj = sj.y;
-    const double c = ei * ej + fi * fj, s = fi * ej - ei * fj;
-    if (dva) { dp = G * s - Bv * c; dq = -(G * c + Bv * s); }
-    else {
-      const double vj = vm[j];
-      dp = (G * c + Bv * s) / vj;
-      dq = (G * s - Bv * c) / vj;
-    }
+// The value of one entry, by the same operations on every path (the fused ones
+// written out), so that neither rounding nor zero, infinite or NaN magnitudes
+// depend on where the state is held: bus i (ei, fi, Pi, Qi), bus j (ej, fj)
+// and |V| of bus j
+__device__ __forceinline__ double entry_value(int kind, bool diag, double G, double B, double2 vi, double2 si,
+                                              double2 vj, double magj) {
+#pragma clang fp contract(off)
+  const bool dva = kind == BK_DP_DVA || kind == BK_DQ_DVA, dp = kind == BK_DP_DVM || kind == BK_DP_DVA;
+  double x;
+  if (!diag) {
+    const double c = fma(vi.x, vj.x, vi.y * vj.y), s = fma(vi.y, vj.x, -(vi.x * vj.y));
+    const double gs_bc = fma(G, s, -(B * c)), gc_bs = fma(G, c, B * s);
+    if (dva) x = dp ? gs_bc : -gc_bs;
+    else x = (dp ? gc_bs : gs_bc) / magj;
   } else {
-    const double vi = vm[i];
-    const double P = si.z, Q = si.w;
-    if (dva) { dp = -Q - Bv * vi * vi; dq = P - G * vi * vi; }
-    else { dp = P / vi + G * vi; dq = Q / vi - Bv * vi; }
+    if (dva) x = dp ? fma(-magj, B * magj, -si.y) : fma(-magj, G * magj, si.x);
+    else x = dp ? fma(G, magj, si.x / magj) : fma(-B, magj, si.y / magj);
   }
-  return -((kind == BK_DP_DVM || kind == BK_DP_DVA) ? dp : dq);
+  return -x;
 }
 
 // thread = (value of the operator, group of kOpGroup scenarios): the
@@ -92,34 +86,41 @@ __global__ void __launch_bounds__(256) k_operator_values(OpParams p) {
   const double G = (kind != BK_SEL && q >= 0) ? p.y_g[q] : 0.0;
   const double Bv = (kind != BK_SEL && q >= 0) ? p.y_b[q] : 0.0;
   const size_t b1 = min((size_t)p.count, (g + 1) * kOpGroup);
-  for (size_t b = g * kOpGroup; b < b1; ++b)
-    p.values[b * p.nnz + v] = kind == BK_SEL ? 1.0 : entry_value(p, kind, i, j, G, Bv, b);
+  for (size_t b = g * kOpGroup; b < b1; ++b) {
+    double x = 1.0;
+    if (kind != BK_SEL) {
+      const double4* st = reinterpret_cast<const double4*>(p.ef) + b * p.n_bus;
+      const double4 si = st[i];
+      double2 vj = make_double2(0.0, 0.0);
+      if (i != j) vj = *reinterpret_cast<const double2*>(st + j);
+      const double magj = p.vm[b * p.n_bus + j];
+      x = entry_value(kind, i == j, G, Bv, make_double2(si.x, si.y), make_double2(si.z, si.w), vj, magj);
+    }
+    p.values[b * p.nnz + v] = x;
+  }
 }
 
 // The same with the state in LDS.  A workgroup owns SC scenarios and one of
-// `splits` runs of the operator's values: it forms cos, sin, |V| of every bus
-// and the current I = Y V there, then evaluates its values from LDS alone, so
-// that the random gathers of a bus pair cost LDS cycles instead of cache
-// lines.  With u = (cos theta, sin theta) the entries need no division:
-// V_j / |V_j| = u_j and S_i / |V_i| = u_i conj(I_i).
+// `splits` runs of the operator's values: it forms the voltage, |V| and the
+// injection of every bus there, then evaluates its values from LDS alone, so
+// that the random gathers of a bus pair cost LDS cycles instead of cache lines.
 // Bound: the write of the values (8 bytes each), behind 32 bytes of pattern
 // per value (record and Y_bus entry) from L2, shared by the SC scenarios.
 // J1, J1^T, J2^T and J3^T of 1024 scenarios of the 1354-bus grid (308 MB of
 // values, 65 us at the rate of a large copy): 493 us with the state in device
-// memory (two launches per operator), 201 us here with two scenarios per
-// workgroup, about 235 us with one.
-constexpr int kOpBusDoubles = 5;   // (cos, sin), (I_re, I_im), |V|
+// memory (two launches per operator), 218 us here with two scenarios per
+// workgroup.  (Division-free forms of the d/d|V| entries took 201 us, but
+// rounded differently and gave values where |V| = 0 has none.)
+constexpr int kOpBusDoubles = 5;   // (e, f), (P, Q), |V|
 
 template <int SC, int NT>
 __global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
-  // the sums below are written with their fused operations, so that a value
-  // does not depend on how many scenarios share its workgroup
 #pragma clang fp contract(off)
   extern __shared__ __align__(16) double op_smem[];
   const int n = p.n_bus, tid = threadIdx.x;
-  double2* u = reinterpret_cast<double2*>(op_smem);        // [n][SC]
-  double2* cur = u + (size_t)n * SC;                       // [n][SC]
-  double* mag = reinterpret_cast<double*>(cur + (size_t)n * SC);
+  double2* v2 = reinterpret_cast<double2*>(op_smem);       // [n][SC]
+  double2* pq = v2 + (size_t)n * SC;                       // [n][SC]
+  double* mag = reinterpret_cast<double*>(pq + (size_t)n * SC);
   const int group = blockIdx.x / splits, split = blockIdx.x - group * splits;
   const int b0 = group * SC;
   for (int q = tid; q < n * SC; q += NT) {
@@ -130,7 +131,7 @@ __global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
       sincos(p.va[o], &sn, &cs);
       v = p.vm[o];
     }
-    u[i * SC + s] = make_double2(cs, sn);
+    v2[i * SC + s] = make_double2(v * cs, v * sn);
     mag[i * SC + s] = v;
   }
   __syncthreads();
@@ -143,14 +144,16 @@ __global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
       const double g = p.y_g[k], b = p.y_b[k];
 #pragma unroll
       for (int s = 0; s < SC; ++s) {
-        const double2 w = u[j * SC + s];
-        const double v = mag[j * SC + s], e = v * w.x, f = v * w.y;
-        ir[s] = fma(-b, f, fma(g, e, ir[s]));
-        ii[s] = fma(b, e, fma(g, f, ii[s]));
+        const double2 w = v2[j * SC + s];
+        ir[s] += fma(g, w.x, -(b * w.y));
+        ii[s] += fma(g, w.y, b * w.x);
       }
     }
 #pragma unroll
-    for (int s = 0; s < SC; ++s) cur[i * SC + s] = make_double2(ir[s], ii[s]);
+    for (int s = 0; s < SC; ++s) {
+      const double2 w = v2[i * SC + s];
+      pq[i * SC + s] = make_double2(fma(w.y, ii[s], w.x * ir[s]), fma(w.y, ir[s], -(w.x * ii[s])));
+    }
   }
   __syncthreads();
   const int per = (p.nnz + splits - 1) / splits;
@@ -160,28 +163,10 @@ __global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
     const int kind = r.x, i = r.y, j = r.z;
     const bool sel = kind == BK_SEL, y = !sel && r.w >= 0;
     const double G = y ? p.y_g[r.w] : 0.0, B = y ? p.y_b[r.w] : 0.0;
-    const bool dva = kind == BK_DP_DVA || kind == BK_DQ_DVA;
-    // dP/dtheta and dQ/d|V| share one form, dQ/dtheta and dP/d|V| the other
-    const bool first = kind == BK_DP_DVA || kind == BK_DQ_DVM;
 #pragma unroll
     for (int s = 0; s < SC; ++s) {
       if (b0 + s >= p.count) break;
-      const double2 wi = u[i * SC + s];
-      const double vi = mag[i * SC + s];
-      double x;
-      if (i != j) {
-        const double2 wj = u[j * SC + s];
-        const double cc = fma(wi.x, wj.x, wi.y * wj.y), ss = fma(wi.y, wj.x, -(wi.x * wj.y));
-        const double w = dva ? vi * mag[j * SC + s] : vi;
-        const double t = first ? fma(B, cc, -(G * ss)) : fma(G, cc, B * ss);
-        x = w * (kind == BK_DP_DVM ? -t : t);
-      } else {
-        const double2 I = cur[i * SC + s];
-        const double a = fma(wi.x, I.x, wi.y * I.y);       // P / |V|
-        const double q = fma(wi.y, I.x, -(wi.x * I.y));    // Q / |V|
-        if (dva) x = vi * (first ? fma(B, vi, q) : fma(G, vi, -a));
-        else x = first ? fma(B, vi, -q) : -fma(G, vi, a);
-      }
+      const double x = entry_value(kind, i == j, G, B, v2[i * SC + s], pq[i * SC + s], v2[j * SC + s], mag[j * SC + s]);
       p.values[(size_t)(b0 + s) * p.nnz + v] = sel ? 1.0 : x;
     }
   }
