@@ -111,9 +111,14 @@ __global__ void __launch_bounds__(256) k_operator_values(OpParams p) {
 // memory (two launches per operator), 218 us here with two scenarios per
 // workgroup.  (Division-free forms of the d/d|V| entries took 201 us, but
 // rounded differently and gave values where |V| = 0 has none.)
+// OWN: where a scenario's values are split over several workgroups, each would
+// form the injections of all buses for the few diagonal entries it has, all of
+// them one after the other in front of its values (3900 buses, one scenario: 73
+// us for the four operators, 67 by the two-launch path); there a diagonal entry
+// forms its own bus's (49 us).
 constexpr int kOpBusDoubles = 5;   // (e, f), (P, Q), |V|
 
-template <int SC, int NT>
+template <int SC, int NT, bool OWN>
 __global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
 #pragma clang fp contract(off)
   extern __shared__ __align__(16) double op_smem[];
@@ -135,7 +140,7 @@ __global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
     mag[i * SC + s] = v;
   }
   __syncthreads();
-  for (int i = tid; i < n; i += NT) {
+  auto injection = [&](int i, double2 (&out)[SC]) {   // (P, Q) of bus i
     double ir[SC], ii[SC];
 #pragma unroll
     for (int s = 0; s < SC; ++s) ir[s] = ii[s] = 0.0;
@@ -152,10 +157,18 @@ __global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
 #pragma unroll
     for (int s = 0; s < SC; ++s) {
       const double2 w = v2[i * SC + s];
-      pq[i * SC + s] = make_double2(fma(w.y, ii[s], w.x * ir[s]), fma(w.y, ir[s], -(w.x * ii[s])));
+      out[s] = make_double2(fma(w.y, ii[s], w.x * ir[s]), fma(w.y, ir[s], -(w.x * ii[s])));
     }
+  };
+  if (!OWN) {
+    for (int i = tid; i < n; i += NT) {
+      double2 x[SC];
+      injection(i, x);
+#pragma unroll
+      for (int s = 0; s < SC; ++s) pq[i * SC + s] = x[s];
+    }
+    __syncthreads();
   }
-  __syncthreads();
   const int per = (p.nnz + splits - 1) / splits;
   const int v1 = min(p.nnz, (split + 1) * per);
   for (int v = split * per + tid; v < v1; v += NT) {
@@ -163,10 +176,13 @@ __global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
     const int kind = r.x, i = r.y, j = r.z;
     const bool sel = kind == BK_SEL, y = !sel && r.w >= 0;
     const double G = y ? p.y_g[r.w] : 0.0, B = y ? p.y_b[r.w] : 0.0;
+    double2 own[SC] = {};
+    if (OWN && i == j && !sel) injection(i, own);
 #pragma unroll
     for (int s = 0; s < SC; ++s) {
       if (b0 + s >= p.count) break;
-      const double x = entry_value(kind, i == j, G, B, v2[i * SC + s], pq[i * SC + s], v2[j * SC + s], mag[j * SC + s]);
+      if (!OWN) own[s] = pq[i * SC + s];
+      const double x = entry_value(kind, i == j, G, B, v2[i * SC + s], own[s], v2[j * SC + s], mag[j * SC + s]);
       p.values[(size_t)(b0 + s) * p.nnz + v] = sel ? 1.0 : x;
     }
   }
@@ -181,10 +197,12 @@ bool operator_state_in_lds(int n_bus) {
 hipError_t set_operator_lds(int n_bus) {
   if (2 * (size_t)n_bus * kOpBusDoubles * sizeof(double) <= 64 * 1024) return hipSuccess;   // the default limit
   hipError_t e = hipSuccess;
-  for (const void* f : {reinterpret_cast<const void*>(&k_operator_lds<1, 512>),
-                        reinterpret_cast<const void*>(&k_operator_lds<2, 512>),
-                        reinterpret_cast<const void*>(&k_operator_lds<1, 1024>),
-                        reinterpret_cast<const void*>(&k_operator_lds<2, 1024>)}) {
+  for (const void* f : {reinterpret_cast<const void*>(&k_operator_lds<1, 512, false>),
+                        reinterpret_cast<const void*>(&k_operator_lds<1, 512, true>),
+                        reinterpret_cast<const void*>(&k_operator_lds<2, 512, false>),
+                        reinterpret_cast<const void*>(&k_operator_lds<1, 1024, false>),
+                        reinterpret_cast<const void*>(&k_operator_lds<1, 1024, true>),
+                        reinterpret_cast<const void*>(&k_operator_lds<2, 1024, false>)}) {
     const hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOpLdsLimit);
     if (r != hipSuccess) e = r;
   }
@@ -207,11 +225,20 @@ hipError_t launch_operator_values(const OpParams& p, hipStream_t st) {
     const int nt = p.n_bus >= 512 ? 1024 : 512;
     const int groups = (p.count + sc - 1) / sc;
     const int splits = std::max(1, std::min((p.nnz + nt - 1) / nt, kCus / groups));
+    // each diagonal entry forms its bus's injection from four splits on (3900
+    // buses x64, four splits: 118 us against 126; x120, two: 192 against 160)
+    const bool own = splits >= 4;
     const dim3 g((unsigned)((size_t)groups * splits)), b(nt);
-    if (sc == 1 && nt == 512) hipLaunchKernelGGL((k_operator_lds<1, 512>), g, b, bus, st, p, splits);
-    else if (sc == 2 && nt == 512) hipLaunchKernelGGL((k_operator_lds<2, 512>), g, b, 2 * bus, st, p, splits);
-    else if (sc == 1) hipLaunchKernelGGL((k_operator_lds<1, 1024>), g, b, bus, st, p, splits);
-    else hipLaunchKernelGGL((k_operator_lds<2, 1024>), g, b, 2 * bus, st, p, splits);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, sc * bus, st, p, splits); };
+    if (nt == 512) {
+      if (sc == 2) launch(k_operator_lds<2, 512, false>);
+      else if (own) launch(k_operator_lds<1, 512, true>);
+      else launch(k_operator_lds<1, 512, false>);
+    } else {
+      if (sc == 2) launch(k_operator_lds<2, 1024, false>);
+      else if (own) launch(k_operator_lds<1, 1024, true>);
+      else launch(k_operator_lds<1, 1024, false>);
+    }
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_operator_state, dim3((unsigned)((nst + 255) / 256)), dim3(256), 0, st, p);

@@ -1,5 +1,5 @@
-"""Operator values at unusual voltage states: zero, infinite, NaN and tiny
-magnitudes at some buses.  The values are those of the documented entry
+"""Operator values at unusual voltage states (zero, infinite, NaN and tiny
+magnitudes at some buses) and at the edges of the launch rules.  The values are those of the documented entry
 formulas (rectangular products, d/d|V| entries divided by the magnitude of the
 column's bus), so where a formula has no value the result is NaN, and it does
 not depend on whether the per-bus state is held in LDS (up to 4096 buses) or in
@@ -75,3 +75,27 @@ def test_special_magnitudes_follow_the_entry_formulas(n, bad, device):
     with np.errstate(all="ignore"):
         for b in range(3):
             _compare(got[b], j1_values(net, pat["indptr"], pat["indices"], vm[b], va[b]))
+
+
+# two scenarios per workgroup up to 2048 buses, state in LDS up to 4096; the
+# values of up to 64 scenarios in four or more splits, where each diagonal entry
+# forms its own bus's injection
+@pytest.mark.parametrize("n,count", [(300, 64), (300, 65), (2048, 513), (2049, 513), (4096, 1), (4096, 64),
+                                     (4096, 65), (4097, 2)])
+def test_values_at_the_edges_of_the_launch_rules(n, count, device):
+    import torch
+    from paper_2606_07099_amd import PFTemplate
+    from paper_2606_07099_amd.pf import PF_OP_J1
+    net = _network(n)
+    tpl = PFTemplate.from_network(net, 1)
+    pat = tpl.operator_pattern(PF_OP_J1)
+    rng = np.random.default_rng(9)
+    vm, va = 1 + 0.03 * rng.standard_normal((count, n)), 0.2 * rng.standard_normal((count, n))
+    tvm, tva = to_dev(vm, device), to_dev(va, device)
+    out = tpl.operator(PF_OP_J1, tvm, tva)
+    out.values().fill_(float("nan"))
+    got = tpl.operator(PF_OP_J1, tvm, tva, out=out).values()
+    torch.cuda.synchronize()
+    assert not bool(torch.isnan(got).any())
+    for b in sorted({0, count // 2, count - 1}):
+        _compare(got.view(count, -1)[b].cpu().numpy(), j1_values(net, pat["indptr"], pat["indices"], vm[b], va[b]))
