@@ -118,17 +118,17 @@ __global__ void __launch_bounds__(256) k_operator_values(OpParams p) {
 // forms its own bus's (49 us).
 constexpr int kOpBusDoubles = 5;   // (e, f), (P, Q), |V|
 
-template <int SC, int NT, bool OWN>
-__global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
+template <int SC, bool OWN>
+__global__ void __launch_bounds__(1024) k_operator_lds(OpParams p, int splits) {
 #pragma clang fp contract(off)
   extern __shared__ __align__(16) double op_smem[];
-  const int n = p.n_bus, tid = threadIdx.x;
+  const int n = p.n_bus, tid = threadIdx.x, nt = blockDim.x;
   double2* v2 = reinterpret_cast<double2*>(op_smem);       // [n][SC]
   double2* pq = v2 + (size_t)n * SC;                       // [n][SC]
   double* mag = reinterpret_cast<double*>(pq + (size_t)n * SC);
   const int group = blockIdx.x / splits, split = blockIdx.x - group * splits;
   const int b0 = group * SC;
-  for (int q = tid; q < n * SC; q += NT) {
+  for (int q = tid; q < n * SC; q += nt) {
     const int s = q / n, i = q - s * n;
     double sn = 0.0, cs = 1.0, v = 1.0;
     if (b0 + s < p.count) {
@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
     }
   };
   if (!OWN) {
-    for (int i = tid; i < n; i += NT) {
+    for (int i = tid; i < n; i += nt) {
       double2 x[SC];
       injection(i, x);
 #pragma unroll
@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(NT) k_operator_lds(OpParams p, int splits) {
   }
   const int per = (p.nnz + splits - 1) / splits;
   const int v1 = min(p.nnz, (split + 1) * per);
-  for (int v = split * per + tid; v < v1; v += NT) {
+  for (int v = split * per + tid; v < v1; v += nt) {
     const int4 r = p.rec[v];
     const int kind = r.x, i = r.y, j = r.z;
     const bool sel = kind == BK_SEL, y = !sel && r.w >= 0;
@@ -197,12 +197,9 @@ bool operator_state_in_lds(int n_bus) {
 hipError_t set_operator_lds(int n_bus) {
   if (2 * (size_t)n_bus * kOpBusDoubles * sizeof(double) <= 64 * 1024) return hipSuccess;   // the default limit
   hipError_t e = hipSuccess;
-  for (const void* f : {reinterpret_cast<const void*>(&k_operator_lds<1, 512, false>),
-                        reinterpret_cast<const void*>(&k_operator_lds<1, 512, true>),
-                        reinterpret_cast<const void*>(&k_operator_lds<2, 512, false>),
-                        reinterpret_cast<const void*>(&k_operator_lds<1, 1024, false>),
-                        reinterpret_cast<const void*>(&k_operator_lds<1, 1024, true>),
-                        reinterpret_cast<const void*>(&k_operator_lds<2, 1024, false>)}) {
+  for (const void* f : {reinterpret_cast<const void*>(&k_operator_lds<1, false>),
+                        reinterpret_cast<const void*>(&k_operator_lds<1, true>),
+                        reinterpret_cast<const void*>(&k_operator_lds<2, false>)}) {
     const hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOpLdsLimit);
     if (r != hipSuccess) e = r;
   }
@@ -214,15 +211,18 @@ hipError_t launch_operator_values(const OpParams& p, hipStream_t st) {
   if (total == 0) return hipSuccess;
   if (operator_state_in_lds(p.n_bus)) {
     // two scenarios per workgroup where that still leaves one per compute
-    // unit; 1024 threads per workgroup from 512 buses on (118 buses x4096:
-    // 67 us with 512, 84 with 1024; 1354 buses x1024: 234 and 177, on one set
-    // of buffers), and the
-    // values of few scenarios split over as many workgroups as there are
-    // compute units
+    // unit, and the values of few scenarios split over as many workgroups as
+    // there are compute units.  Threads: at least one and a half per bus, as a
+    // power of two from a wavefront to 512, and 1024 from 512 buses on.  The four operators of 14 buses x60000 took
+    // 454 us with 512 threads, most of them idle, against 166 with 64 (two
+    // launches: 222); 30 buses x40000 359 and 164; 60 x20000 237 and 152 (128);
+    // 118 x11000 184 and 159 (256), where 64 take 217; 300 x4000 154 with 512,
+    // 169 with 256; 1354 x1024 (one set of buffers) 234 with 512, 177 with 1024
     constexpr int kCus = 256;
     const size_t bus = kOpBusDoubles * sizeof(double) * (size_t)p.n_bus;
     const int sc = p.count >= 2 * kCus && 2 * bus <= kOpLdsLimit ? 2 : 1;
-    const int nt = p.n_bus >= 512 ? 1024 : 512;
+    int nt = p.n_bus >= 512 ? 1024 : 64;
+    while (nt < 512 && 2 * nt < 3 * p.n_bus) nt *= 2;
     const int groups = (p.count + sc - 1) / sc;
     const int splits = std::max(1, std::min((p.nnz + nt - 1) / nt, kCus / groups));
     // each diagonal entry forms its bus's injection from four splits on (3900
@@ -230,15 +230,9 @@ hipError_t launch_operator_values(const OpParams& p, hipStream_t st) {
     const bool own = splits >= 4;
     const dim3 g((unsigned)((size_t)groups * splits)), b(nt);
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, sc * bus, st, p, splits); };
-    if (nt == 512) {
-      if (sc == 2) launch(k_operator_lds<2, 512, false>);
-      else if (own) launch(k_operator_lds<1, 512, true>);
-      else launch(k_operator_lds<1, 512, false>);
-    } else {
-      if (sc == 2) launch(k_operator_lds<2, 1024, false>);
-      else if (own) launch(k_operator_lds<1, 1024, true>);
-      else launch(k_operator_lds<1, 1024, false>);
-    }
+    if (sc == 2) launch(k_operator_lds<2, false>);
+    else if (own) launch(k_operator_lds<1, true>);
+    else launch(k_operator_lds<1, false>);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_operator_state, dim3((unsigned)((nst + 255) / 256)), dim3(256), 0, st, p);

@@ -99,3 +99,10 @@ def test_values_at_the_edges_of_the_launch_rules(n, count, device):
     assert not bool(torch.isnan(got).any())
     for b in sorted({0, count // 2, count - 1}):
         _compare(got.view(count, -1)[b].cpu().numpy(), j1_values(net, pat["indptr"], pat["indices"], vm[b], va[b]))
+
+
+# workgroups of 64, 128, 256, 512 and 1024 threads, one and two scenarios each
+@pytest.mark.parametrize("count", [7, 515])
+@pytest.mark.parametrize("n", [14, 42, 43, 85, 86, 170, 171, 511, 512])
+def test_values_with_every_workgroup_size(n, count, device):
+    test_values_at_the_edges_of_the_launch_rules(n, count, device)
