@@ -1,0 +1,96 @@
+// Launch plan of HBM-resident templates (declared in hbm_plan.h).
+#include "hbm_plan.h"
+
+#include <algorithm>
+
+#include "sable_pf.h"
+
+namespace sable {
+
+namespace {
+
+// the plan for slices of p.slice scenarios that factor row by row (p.rows) or
+// by levels in place, with y in LDS where that leaves the full metadata budget
+// (if want_y)
+int plan_slice(const Symbolic& S, const HbmShape& h, bool want_y, HbmPlan& p, std::string& err) {
+  const int sl = p.slice;
+  const size_t tsz = h.fp32 ? 4 : 8;
+  const size_t upd_words = S.tail_prog.size() - (size_t)S.tail_prog_prefix;
+  const size_t prefix_bytes = (4 * (size_t)S.tail_prog_prefix + 15) / 16 * 16;
+  const size_t fixed = kScratchBytes + prefix_bytes;
+  const size_t tail_bytes = tail_copy_bytes(S, sl, h.fp32);
+  // what the metadata can have beside the tail copy (S > 1: at most half of it
+  // where rows need buffers) and, when that leaves the full metadata budget,
+  // beside y: every solve's gathers then stay on chip
+  if (fixed + tail_bytes + 4 * 2048 > h.max_lds) {
+    err = "pf_template_build: the dense tail does not fit in LDS";
+    return PF_EINVAL;
+  }
+  size_t room = h.max_lds - fixed - tail_bytes;
+  p.y_bytes = want_y ? ((size_t)2 * S.nb * sl * tsz + 15) / 16 * 16 : 0;
+  const int32_t want = p.rows && sl > 1 ? kChunkInts / 2 : kChunkInts;
+  if (room >= p.y_bytes + 4 * (size_t)want) room -= p.y_bytes;
+  else p.y_bytes = 0;
+  const int32_t budget = (int32_t)std::min<size_t>(want, room / 16 * 4);
+  p.st = p.rows ? storage_split(S) : storage_by_position(S);
+  int rc = build_level_chunks(S, budget, p.chunks, err, &p.st);
+  if (rc != 0) return rc;
+  // the tail's update words are staged in the metadata area (free while the
+  // tail is factored) when the area, grown within the room, holds them
+  p.tail_prog_lds = (upd_words + 3) / 4 * 16 <= room;
+  p.chunk_ints = std::max<int>(p.chunks.max_ints, p.tail_prog_lds ? (int)(upd_words + 3) / 4 * 4 : 0);
+  p.row_chunks = RowChunks{};
+  p.flow = FlowTasks{};
+  p.area = tail_bytes;
+  if (p.rows) {
+    p.chunk_ints = std::max(p.chunk_ints, budget);
+    p.area = h.max_lds - fixed - p.y_bytes - 4 * (size_t)p.chunk_ints;
+    if (sl == 1) {
+      // wavefront tasks, each wavefront with its share of the buffers and of
+      // the metadata area, behind which the levels are counted
+      const int waves = h.threads / 64, counts = (S.n_fs_levels + 2 + 3) / 4 * 4;
+      p.flow_buf = (int)(p.area / (4 * tsz)) / waves;
+      p.flow_meta = std::min<int>(kFlowMaxWords, std::max(0, p.chunk_ints - counts) / waves / 4 * 4);
+      rc = build_flow_tasks(S, p.st, waves, p.flow_buf, p.flow_meta, p.flow, err);
+    } else {
+      rc = build_row_chunks(S, p.st, sl, h.threads, (int64_t)(p.area / (4 * tsz * sl)), budget, p.row_chunks, err);
+    }
+    if (rc != 0) return rc;
+  }
+  p.tail_off = fixed + 4 * (size_t)p.chunk_ints;
+  p.lds_bytes = (p.tail_off + p.area + 15) / 16 * 16;
+  p.y_off = p.y_bytes ? p.lds_bytes : 0;
+  p.lds_bytes += p.y_bytes;
+  return 0;
+}
+
+}  // namespace
+
+int plan_hbm(const Symbolic& S, const HbmShape& h, HbmPlan& p, std::string& err) {
+  // S scenarios interleaved per slice, S as large as keeps at least one slice
+  // per compute unit and leaves room in LDS for the tail copy and for staged
+  // metadata; S = 1 always fits: the tail holds at most 32 x 32 blocks.  The
+  // rows of the row-by-row factorisation have to fit beside the metadata too
+  // (in the place of the tail copy, which is made after it); where they do not,
+  // y gives way to them, and a network with a row too long for that even with
+  // S = 1 factors by levels in place.
+  p = HbmPlan{};
+  while (p.slice < kMaxSlice && h.batch / (2 * p.slice) >= h.n_cu) p.slice *= 2;
+  // Slices of one scenario with FP32 factors factor by levels in place on the
+  // smaller grids: there a levelled pass costs little more than its barrier
+  // (1354 buses x250, mixed: 1.55 ms by levels, 1.65 by rows; FP64 0.97 both;
+  // 300 buses x250, FP64: 0.36 and 0.34; 9241 buses x256, mixed: 9.4 and 8.8,
+  // FP64 9.6 and 6.5).
+  const bool by_levels = h.fp32 && S.nb < 4096;
+  int rc = PF_EINVAL;
+  for (p.rows = true;; p.slice /= 2) {
+    if (p.slice > 1 || !by_levels)
+      for (const bool y : {true, false})
+        if ((rc = plan_slice(S, h, y, p, err)) == 0) return 0;
+    if (p.slice == 1) break;
+  }
+  p.rows = false;
+  return plan_slice(S, h, true, p, err);
+}
+
+}  // namespace sable

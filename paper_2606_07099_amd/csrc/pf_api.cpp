@@ -85,10 +85,6 @@ struct DeviceGuard {
   ~DeviceGuard() { if (prev >= 0) (void)hipSetDevice(prev); }
 };
 
-// largest level-metadata chunk an HBM-resident workgroup stages in LDS
-// (int32 words; 48 KB)
-constexpr int32_t kChunkInts = 12288;
-
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 // HBM workspace of a scenario (also the layout of the interleaved slice
@@ -400,15 +396,9 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
   pf_template* t = new (std::nothrow) pf_template();
   if (!t) return fail(PF_ENOMEM, "pf_template_build: host allocation failed");
   std::string err;
-  // the dense tail of an LDS-resident slice lives in registers: at most 32
-  // block rows in FP32, 16 in FP64
-  const int tail_max = opt.precision == PF_MIXED ? 32 : 16;
-  // and an FP64 tail takes in levels of at most four rows: a row costs the tail
-  // 0.7 us per factorisation, a level outside it 2.6 us per update (factor and
-  // backward pass), which the tail's wavefront alone no longer beats.  With FP32
-  // factors a level also costs the refinement's four solves, a tail row less.
-  const int tail_level = opt.precision == PF_MIXED ? tail_max : 4;
-  int rc = sable::analyze(n_bus, bus_type, y_indptr, y_indices, y_g, y_b, t->sym, err, tail_max, tail_level);
+  t->fp32 = opt.precision == PF_MIXED;
+  int rc = sable::analyze(n_bus, bus_type, y_indptr, y_indices, y_g, y_b, t->sym, err, sable::tail_max_rows(t->fp32),
+                          sable::tail_max_level(t->fp32));
   if (rc != PF_OK) { delete t; return fail(rc, err); }
   if (!structurally_symmetric(t->sym)) {
     delete t;
@@ -417,7 +407,6 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
   const sable::Symbolic& S = t->sym;
   t->opt = opt;
   t->batch = batch;
-  t->fp32 = opt.precision == PF_MIXED;
   const size_t tsz = t->fp32 ? 4 : 8;
 
   hipError_t he = hipGetDevice(&t->device);
@@ -442,17 +431,10 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
   dm.nlev_f = S.n_task_levels; dm.nlev_fs = S.n_fs_levels;
   dm.nlev_bs = (int)S.lev_um_ptr.size() - 1;
   dm.tail_t = S.tail_t; dm.tail_base = S.tail_base;
-  // the LDS copy of the tail: per scenario its tail-column blocks (stride
-  // odd, so that the scenarios' copies start in different banks), pivot
-  // inverses and right-hand sides; the tail program's solve prefix
-  const size_t tail_nbs = S.tail_cblk.size() | 1;
-  dm.tail_nbs = (int)tail_nbs;
+  dm.tail_nbs = (int)sable::tail_copy_stride(S);
   dm.tail_nblk = (int)S.tail_cblk.size();
   dm.tail_prog_ints = (int)S.tail_prog.size();
   dm.tail_prog_prefix = S.tail_prog_prefix;
-  const size_t upd_words = S.tail_prog.size() - (size_t)S.tail_prog_prefix;
-  const size_t prefix_bytes = (4 * (size_t)S.tail_prog_prefix + 15) / 16 * 16;
-  auto tail_bytes = [&](int sl) { return (size_t)sl * tsz * (4 * tail_nbs + 6 * (size_t)S.tail_t); };
 
   // packs the device image for one storage of the blocks
   auto pack = [&](const sable::LuStorage& st, const sable::LevelChunks& chunks, const sable::RowChunks* rows,
@@ -536,7 +518,7 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
     // level metadata read in place from the LDS image
     sable::LevelChunks chunks;
     const sable::LuStorage st = sable::storage_by_position(S);
-    if (sable::build_level_chunks(S, kChunkInts, chunks, err, &st) == 0) {
+    if (sable::build_level_chunks(S, sable::kChunkInts, chunks, err, &st) == 0) {
       pk = pack(st, chunks, nullptr, nullptr);
       for (int sl : {4, 2, 1}) {
         if (sl > sable::kResMaxSlice) continue;
@@ -565,97 +547,37 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
     t->lds_bytes = sable::kScratchBytes + (size_t)so.newton_bytes + best_s * per_scen;
     nt = res_nt;
   } else {
-    // HBM-resident: S scenarios interleaved per slice, S as large as keeps at
-    // least one slice per compute unit and leaves room in LDS for the tail
-    // copy and for staged metadata; S = 1 always fits: the tail holds at most
-    // 32 x 32 blocks.  The rows of the row-by-row factorisation have to fit
-    // beside the metadata too (in the place of the tail copy, which is made
-    // after it); a network with a row too long for that even with S = 1
-    // (thousands of neighbours) factors by levels in place.
+    // HBM-resident
     t->lds_res = false;
     // a full workgroup of 16 wavefronts: measured fastest for every slice
     // width (more lanes per level of the elimination schedule)
     if (nt == 0) nt = 1024;
-    const int n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    int sl = 1;
-    while (sl < sable::kMaxSlice && batch / (2 * sl) >= n_cu) sl *= 2;
-    sable::LevelChunks chunks;
-    sable::RowChunks rows;
-    sable::FlowTasks flow;
-    const size_t fixed = sable::kScratchBytes + prefix_bytes;
-    size_t y_bytes = 0, area = 0;
-    int32_t budget = 0;
-    auto plan = [&](bool by_rows) -> int {
-      // what the metadata can have beside the tail copy (S > 1: at most half
-      // of it where rows need buffers) and, when that leaves the full metadata
-      // budget, beside the slice's right-hand side / solution vector y: every
-      // solve's gathers then stay on chip
-      if (fixed + tail_bytes(sl) + 4 * 2048 > max_lds) { err = "pf_template_build: the dense tail does not fit in LDS"; return PF_EINVAL; }
-      size_t room = max_lds - fixed - tail_bytes(sl);
-      y_bytes = ((size_t)2 * S.nb * sl * tsz + 15) / 16 * 16;
-      const int32_t want = by_rows && sl > 1 ? kChunkInts / 2 : kChunkInts;
-      if (room >= y_bytes + 4 * (size_t)want) room -= y_bytes;
-      else y_bytes = 0;
-      budget = (int32_t)std::min<size_t>(want, room / 16 * 4);
-      const sable::LuStorage st = by_rows ? sable::storage_split(S) : sable::storage_by_position(S);
-      int r = sable::build_level_chunks(S, budget, chunks, err, &st);
-      if (r != 0) return r;
-      // the tail's update words are staged in the metadata area (free while
-      // the tail is factored) when the area, grown within the room, holds them
-      dm.tail_prog_lds = (upd_words + 3) / 4 * 16 <= room ? 1 : 0;
-      dm.chunk_ints = std::max<int>(chunks.max_ints, dm.tail_prog_lds ? (int)(upd_words + 3) / 4 * 4 : 0);
-      if (by_rows) {
-        dm.chunk_ints = std::max(dm.chunk_ints, budget);
-        area = max_lds - fixed - y_bytes - 4 * (size_t)dm.chunk_ints;
-        dm.n_flow = dm.flow_levels = 0;
-        rows = sable::RowChunks{};
-        flow = sable::FlowTasks{};
-        if (sl == 1) {
-          // wavefront tasks, each wavefront with its share of the buffers and
-          // of the metadata area, behind which the levels are counted
-          const int waves = nt / 64, counts = (S.n_fs_levels + 2 + 3) / 4 * 4;
-          dm.flow_buf = (int)(area / (4 * tsz)) / waves;
-          dm.flow_meta = std::min<int>(sable::kFlowMaxWords, std::max(0, dm.chunk_ints - counts) / waves / 4 * 4);
-          r = sable::build_flow_tasks(S, st, waves, dm.flow_buf, dm.flow_meta, flow, err);
-          dm.n_flow = flow.n_tasks();
-          dm.flow_levels = (int)flow.per_level.size();
-        } else {
-          r = sable::build_row_chunks(S, st, sl, nt, (int64_t)(area / (4 * tsz * sl)), budget, rows, err);
-        }
-        if (r != 0) return r;
-      } else {
-        area = tail_bytes(sl);
-      }
-      pk = pack(st, chunks, by_rows ? &rows : nullptr, by_rows ? &flow : nullptr);
-      return 0;
-    };
-    // Slices of one scenario with FP32 factors factor by levels in place on the
-    // smaller grids: there a levelled pass costs little more than its barrier
-    // (1354 buses x250, mixed: 1.55 ms by levels, 1.65 by rows; FP64 0.97 both;
-    // 300 buses x250, FP64: 0.36 and 0.34; 9241 buses x256, mixed: 9.4 and 8.8,
-    // FP64 9.6 and 6.5).
-    t->rows = true;
-    const bool by_levels = t->fp32 && S.nb < 4096;
-    while ((rc = sl == 1 && by_levels ? PF_EINVAL : plan(true)) != 0 && sl > 1) sl /= 2;
-    if (rc != 0) {
-      t->rows = false;
-      sl = 1;
-      rc = plan(false);
-    }
+    sable::HbmShape shape;
+    shape.batch = batch;
+    shape.threads = nt;
+    shape.n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+    shape.max_lds = max_lds;
+    shape.fp32 = t->fp32;
+    sable::HbmPlan plan;
+    rc = sable::plan_hbm(S, shape, plan, err);
     if (rc != 0) { delete t; return fail(PF_EINVAL, err); }
-    t->slice = sl;
+    pk = pack(plan.st, plan.chunks, plan.rows ? &plan.row_chunks : nullptr, plan.rows ? &plan.flow : nullptr);
+    t->rows = plan.rows;
+    t->slice = plan.slice;
     // grouped per-bus values: a slice of several scenarios reads a bus's
     // values of all of them at once, a slice of one reads them in pairs
-    t->lay = make_layout(S.n_bus, S.nb, S.nnzb(), sl > 1 ? 8 : 2, t->rows);
-    dm.tail_off = (int)(fixed + 4 * (size_t)dm.chunk_ints);
-    t->lds_bytes = (dm.tail_off + area + 15) / 16 * 16;
-    dm.y_lds_off = 0;
-    if (y_bytes) {
-      dm.y_lds_off = (int)t->lds_bytes;
-      t->lds_bytes += y_bytes;
-    }
+    t->lay = make_layout(S.n_bus, S.nb, S.nnzb(), plan.slice > 1 ? 8 : 2, plan.rows);
+    dm.chunk_ints = plan.chunk_ints;
+    dm.tail_prog_lds = plan.tail_prog_lds ? 1 : 0;
+    dm.n_flow = plan.flow.n_tasks();
+    dm.flow_levels = (int)plan.flow.per_level.size();
+    dm.flow_meta = plan.flow_meta;
+    dm.flow_buf = plan.flow_buf;
+    dm.tail_off = (int)plan.tail_off;
+    dm.y_lds_off = (int)plan.y_off;
+    t->lds_bytes = plan.lds_bytes;
     // the adjoint reads this slice workspace in place
-    t->adj_slice = -sl;
+    t->adj_slice = -plan.slice;
     t->adj_nt = 1024;   // as the Newton kernel: more lanes per level of the transposed solves
     t->adj_lds = t->lds_bytes;
   }

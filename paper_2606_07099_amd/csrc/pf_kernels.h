@@ -7,6 +7,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "hbm_plan.h"
+
 namespace sable {
 
 enum Mode : int {
@@ -48,7 +50,6 @@ enum PhaseSlot : int {
 // scenario) partial maxima and flags, per-scenario reductions, zero-pivot
 // flags and Newton bookkeeping (iterations, status, final mismatch).
 constexpr int kMaxWaves = 16;
-constexpr int kMaxSlice = 16;
 constexpr int kRedOff = 0;                                     // double [16][16]
 constexpr int kFlagOff = kRedOff + 8 * kMaxWaves * kMaxSlice;  // int [16][16]
 constexpr int kPivOff = kFlagOff + 4 * kMaxWaves * kMaxSlice;  // int [16]
@@ -57,7 +58,6 @@ constexpr int kBadOff = kFnOff + 8 * kMaxSlice;                // int [16]
 constexpr int kItOff = kBadOff + 4 * kMaxSlice;                // int [16]
 constexpr int kStOff = kItOff + 4 * kMaxSlice;                 // int [16]
 constexpr int kFnvOff = kStOff + 4 * kMaxSlice;                // double [16]
-constexpr int kScratchBytes = 4096;
 static_assert(kFnvOff + 8 * kMaxSlice <= kScratchBytes, "scratch layout");
 
 // Byte offsets of the symbolic arrays inside one packed image (device

@@ -1,0 +1,55 @@
+"""The launch plan of HBM-resident templates, as ``pf_template_build`` makes it
+(``tests/native/plan_check.cpp``, built with the sanitizers): which path a
+network's factorisation takes, and a replay of its schedule."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from gen.grids import GridSpec, make_network
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2606_07099_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def checker(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    out = str(tmp_path_factory.mktemp("plan") / "plan_check")
+    cmd = [gxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(ROOT, "tests", "native", "plan_check.cpp"),
+           os.path.join(CSRC, "hbm_plan.cpp"), os.path.join(CSRC, "symbolic.cpp"), "-o", out]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return out
+
+
+def grid(n, seed=1):
+    return make_network(GridSpec("sized", 100, n, round(0.3 * n), round(1.4 * n), 1, 0.10, 1e-8, load_factor=0.05),
+                        seed)
+
+
+def write(path, net):
+    with open(path, "w") as fh:
+        fh.write(f"{net.n_bus} {len(net.f)}\n" + " ".join(str(int(v)) for v in net.bus_type) + "\n")
+        for k in range(len(net.f)):
+            fh.write("%d %d %.17g %.17g %.17g\n" % (net.f[k], net.t[k], net.r[k], net.x[k], net.bc[k]))
+    return str(path)
+
+
+def plan(checker, path, precision="fp64", batch=256, threads=1024):
+    r = subprocess.run([checker, path, precision, str(batch), str(threads)], capture_output=True, text=True,
+                       timeout=600)
+    assert r.returncode == 0 and "violations 0" in r.stdout, r.stdout + r.stderr
+    m = re.search(r"path (\w+) slice (\d+) y (\d+) lds (\d+) tail (\d+) longest (\d+) words (\d+)", r.stdout)
+    return dict(zip(("slice", "y", "lds", "tail", "longest", "words"), map(int, m.groups()[1:])), path=m.group(1))
+
+
+@pytest.mark.parametrize("n", [300, 1354, 2600, 4200, 4600, 5000, 5600, 6000, 6600])
+def test_single_scenario_fp64_slices_factor_as_tasks(checker, tmp_path, n):
+    """y in LDS does not crowd out the wavefronts' row buffers."""
+    assert plan(checker, write(tmp_path / "net.txt", grid(n)))["path"] == "tasks"
