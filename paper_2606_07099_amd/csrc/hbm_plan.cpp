@@ -9,10 +9,11 @@ namespace sable {
 
 namespace {
 
-// the plan for slices of p.slice scenarios that factor row by row (p.rows) or
-// by levels in place, with y in LDS where that leaves the full metadata budget
-// (if want_y)
-int plan_slice(const Symbolic& S, const HbmShape& h, bool want_y, HbmPlan& p, std::string& err) {
+// the plan for slices of p.slice scenarios that factor row by row (rows) or by
+// levels in place, with y in LDS where that leaves the full metadata budget (if
+// want_y); waves: wavefronts that take tasks (rows of one scenario)
+int plan_slice(const Symbolic& S, const HbmShape& h, bool rows, bool want_y, int waves, HbmPlan& p,
+               std::string& err) {
   const int sl = p.slice;
   const size_t tsz = h.fp32 ? 4 : 8;
   const size_t upd_words = S.tail_prog.size() - (size_t)S.tail_prog_prefix;
@@ -28,11 +29,11 @@ int plan_slice(const Symbolic& S, const HbmShape& h, bool want_y, HbmPlan& p, st
   }
   size_t room = h.max_lds - fixed - tail_bytes;
   p.y_bytes = want_y ? ((size_t)2 * S.nb * sl * tsz + 15) / 16 * 16 : 0;
-  const int32_t want = p.rows && sl > 1 ? kChunkInts / 2 : kChunkInts;
+  const int32_t want = rows && sl > 1 ? kChunkInts / 2 : kChunkInts;
   if (room >= p.y_bytes + 4 * (size_t)want) room -= p.y_bytes;
   else p.y_bytes = 0;
   const int32_t budget = (int32_t)std::min<size_t>(want, room / 16 * 4);
-  p.st = p.rows ? storage_split(S) : storage_by_position(S);
+  p.st = rows ? storage_split(S) : storage_by_position(S);
   int rc = build_level_chunks(S, budget, p.chunks, err, &p.st);
   if (rc != 0) return rc;
   // the tail's update words are staged in the metadata area (free while the
@@ -42,16 +43,28 @@ int plan_slice(const Symbolic& S, const HbmShape& h, bool want_y, HbmPlan& p, st
   p.row_chunks = RowChunks{};
   p.flow = FlowTasks{};
   p.area = tail_bytes;
-  if (p.rows) {
+  p.factor = rows ? FACTOR_ROWS : FACTOR_LEVELS;
+  if (rows) {
     p.chunk_ints = std::max(p.chunk_ints, budget);
+    if (sl == 1) {
+      // wavefront tasks, each wavefront with its share of the metadata area,
+      // behind which the levels are counted, and of the buffers.  A long row's
+      // record takes more than that share, out of what the buffers would have.
+      const int counts = (S.n_fs_levels + 2 + 3) / 4 * 4;
+      p.flow_waves = waves;
+      p.flow_meta = std::min<int>(kFlowMaxWords, std::max(0, p.chunk_ints - counts) / waves / 4 * 4);
+      p.flow_meta = std::max(p.flow_meta, flow_row_words(S));
+      p.chunk_ints = std::max(p.chunk_ints, counts + waves * p.flow_meta);
+    }
+    if (fixed + p.y_bytes + 4 * (size_t)p.chunk_ints + tail_bytes > h.max_lds) {
+      err = "pf_template_build: the task records do not fit in LDS";
+      return PF_EINVAL;
+    }
     p.area = h.max_lds - fixed - p.y_bytes - 4 * (size_t)p.chunk_ints;
     if (sl == 1) {
-      // wavefront tasks, each wavefront with its share of the buffers and of
-      // the metadata area, behind which the levels are counted
-      const int waves = h.threads / 64, counts = (S.n_fs_levels + 2 + 3) / 4 * 4;
       p.flow_buf = (int)(p.area / (4 * tsz)) / waves;
-      p.flow_meta = std::min<int>(kFlowMaxWords, std::max(0, p.chunk_ints - counts) / waves / 4 * 4);
       rc = build_flow_tasks(S, p.st, waves, p.flow_buf, p.flow_meta, p.flow, err);
+      if (p.flow.max_ints > kFlowMaxWords) p.factor = FACTOR_LONG_ROWS;
     } else {
       rc = build_row_chunks(S, p.st, sl, h.threads, (int64_t)(p.area / (4 * tsz * sl)), budget, p.row_chunks, err);
     }
@@ -72,8 +85,12 @@ int plan_hbm(const Symbolic& S, const HbmShape& h, HbmPlan& p, std::string& err)
   // metadata; S = 1 always fits: the tail holds at most 32 x 32 blocks.  The
   // rows of the row-by-row factorisation have to fit beside the metadata too
   // (in the place of the tail copy, which is made after it); where they do not,
-  // y gives way to them, and a network with a row too long for that even with
-  // S = 1 factors by levels in place.
+  // y gives way to them, and then some of the wavefronts that take tasks.  With
+  // FP32 factors neither does: the refinement solves, which y in LDS is for, are
+  // the larger part (11000 buses, mixed: x250 9.8 ms by levels, 10.2 by tasks
+  // without y, 9.8 by half as many wavefronts, x37 7.0 and 8.1; FP64 x250 10.6
+  // by levels, 6.8 by tasks without y).  A network whose rows do not fit even
+  // with S = 1 (more than 255 blocks) factors by levels in place.
   p = HbmPlan{};
   while (p.slice < kMaxSlice && h.batch / (2 * p.slice) >= h.n_cu) p.slice *= 2;
   // Slices of one scenario with FP32 factors factor by levels in place on the
@@ -83,14 +100,19 @@ int plan_hbm(const Symbolic& S, const HbmShape& h, HbmPlan& p, std::string& err)
   // FP64 9.6 and 6.5).
   const bool by_levels = h.fp32 && S.nb < 4096;
   int rc = PF_EINVAL;
-  for (p.rows = true;; p.slice /= 2) {
-    if (p.slice > 1 || !by_levels)
-      for (const bool y : {true, false})
-        if ((rc = plan_slice(S, h, y, p, err)) == 0) return 0;
+  for (;; p.slice /= 2) {
+    if (p.slice > 1 || !by_levels) {
+      int waves = h.threads / 64;
+      if ((rc = plan_slice(S, h, true, true, waves, p, err)) == 0) return 0;
+      if (!h.fp32) {
+        if ((rc = plan_slice(S, h, true, false, waves, p, err)) == 0) return 0;
+        while (p.slice == 1 && waves > 1)
+          if ((rc = plan_slice(S, h, true, false, waves /= 2, p, err)) == 0) return 0;
+      }
+    }
     if (p.slice == 1) break;
   }
-  p.rows = false;
-  return plan_slice(S, h, true, p, err);
+  return plan_slice(S, h, false, true, 0, p, err);
 }
 
 }  // namespace sable

@@ -32,6 +32,10 @@ constexpr int32_t tail_max_rows(bool fp32) { return fp32 ? 32 : 16; }
 // factors a level also costs the refinement's four solves, a tail row less.
 constexpr int32_t tail_max_level(bool fp32) { return fp32 ? tail_max_rows(true) : 4; }
 
+// How a template factors: by levels in place, or row by row (one scenario per
+// slice: as wavefront tasks); long rows: with task records beyond kFlowMaxWords.
+enum Factoring : int { FACTOR_LEVELS = 0, FACTOR_ROWS = 1, FACTOR_LONG_ROWS = 2 };
+
 struct HbmShape {
   int32_t batch = 1, threads = 1024;
   int32_t n_cu = 256;
@@ -41,13 +45,14 @@ struct HbmShape {
 
 struct HbmPlan {
   int32_t slice = 1;             // scenarios per workgroup
-  bool rows = false;             // factors row by row (one scenario: as wavefront tasks), else by levels in place
+  Factoring factor = FACTOR_LEVELS;
   LuStorage st;
   LevelChunks chunks;
   RowChunks row_chunks;
   FlowTasks flow;
   int32_t chunk_ints = 0;        // words of the metadata area
   bool tail_prog_lds = false;    // the tail program's update words are staged there
+  int32_t flow_waves = 0;        // wavefronts that take tasks
   int32_t flow_buf = 0;          // row buffer of a wavefront, in blocks
   int32_t flow_meta = 0;         // words of a wavefront's task record area
   size_t tail_off = 0;           // byte offset of the row buffers / the tail copy

@@ -25,7 +25,7 @@ struct pf_template {
   bool fp32 = false;
   int nt = 256;
   bool lds_res = false;
-  bool rows = false;         // HBM-resident slices factor row by row
+  sable::Factoring factor = sable::FACTOR_LEVELS;
   size_t lds_bytes = 0;
   int gmin = 4;
   int wstride = 0;
@@ -286,7 +286,7 @@ int adjoint_impl(const char* name, pf_template* t, const double* g_vm, const dou
   const int aw = t->adj_slice < 0 ? -t->adj_slice : t->adj_slice;
   const int agrid = aw ? (t->batch + aw - 1) / aw : t->batch;
   hipError_t he = sable::launch_adjoint(kp, t->fp32, t->adj_slice, agrid, aw ? t->adj_nt : t->nt, t->adj_lds,
-                                        t->rows, static_cast<hipStream_t>(hip_stream));
+                                        t->factor, static_cast<hipStream_t>(hip_stream));
   if (he != hipSuccess) return hip_fail(he, (nm + ": launch").c_str());
   return PF_OK;
 }
@@ -561,16 +561,18 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
     sable::HbmPlan plan;
     rc = sable::plan_hbm(S, shape, plan, err);
     if (rc != 0) { delete t; return fail(PF_EINVAL, err); }
-    pk = pack(plan.st, plan.chunks, plan.rows ? &plan.row_chunks : nullptr, plan.rows ? &plan.flow : nullptr);
-    t->rows = plan.rows;
+    const bool rows = plan.factor != sable::FACTOR_LEVELS;
+    pk = pack(plan.st, plan.chunks, rows ? &plan.row_chunks : nullptr, rows ? &plan.flow : nullptr);
+    t->factor = plan.factor;
     t->slice = plan.slice;
     // grouped per-bus values: a slice of several scenarios reads a bus's
     // values of all of them at once, a slice of one reads them in pairs
-    t->lay = make_layout(S.n_bus, S.nb, S.nnzb(), plan.slice > 1 ? 8 : 2, plan.rows);
+    t->lay = make_layout(S.n_bus, S.nb, S.nnzb(), plan.slice > 1 ? 8 : 2, rows);
     dm.chunk_ints = plan.chunk_ints;
     dm.tail_prog_lds = plan.tail_prog_lds ? 1 : 0;
     dm.n_flow = plan.flow.n_tasks();
     dm.flow_levels = (int)plan.flow.per_level.size();
+    dm.flow_waves = plan.flow_waves;
     dm.flow_meta = plan.flow_meta;
     dm.flow_buf = plan.flow_buf;
     dm.tail_off = (int)plan.tail_off;
@@ -672,7 +674,7 @@ int pf_solve_batch(pf_template* t, const double* pd, const double* qd, const dou
   kp.iters_out = iters; kp.status_out = status; kp.fnorm_out = final_mismatch;
   const int grid = (t->batch + t->slice - 1) / t->slice;
   hipError_t he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res,
-                                       t->rows, static_cast<hipStream_t>(hip_stream));
+                                       t->factor, static_cast<hipStream_t>(hip_stream));
   if (he != hipSuccess) return hip_fail(he, "pf_solve_batch: launch");
   t->have_factors = t->opt.keep_factors != 0;
   return PF_OK;
@@ -726,27 +728,27 @@ int pf_eval_batch(pf_template* t, int32_t mode, int32_t count, const double* pd,
   switch (mode) {
     case PF_EVAL_MISMATCH:
       kp.mode = sable::MODE_EVAL_MISMATCH;
-      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->rows, st);
+      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->factor, st);
       break;
     case PF_EVAL_STEP:
       kp.mode = sable::MODE_EVAL_STEP;
-      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->rows, st);
+      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->factor, st);
       break;
     case PF_EVAL_JACOBIAN:
       he = sable::launch_jacobian_dense(kp, count, st);
       break;
     case PF_EVAL_FILL:
       kp.mode = sable::MODE_EVAL_FILL;
-      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->rows, st);
+      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->factor, st);
       break;
     case PF_EVAL_ADJOINT:
       kp.mode = sable::MODE_EVAL_FACTOR;
-      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->rows, st);
+      he = sable::launch_newton(kp, t->fp32, t->slice, grid, t->nt, t->lds_bytes, t->lds_res, t->factor, st);
       if (he == hipSuccess) {
         kp.mode = sable::MODE_EVAL_ADJOINT;
         const int aw = t->adj_slice < 0 ? -t->adj_slice : t->adj_slice;
         he = sable::launch_adjoint(kp, t->fp32, t->adj_slice, aw ? (count + aw - 1) / aw : count,
-                                   aw ? t->adj_nt : t->nt, t->adj_lds, t->rows, st);
+                                   aw ? t->adj_nt : t->nt, t->adj_lds, t->factor, st);
       }
       break;
     default:

@@ -88,6 +88,7 @@ struct Dims {
   int nch_f, nch_fs, nch_bs;      // metadata chunks of the factor, forward and backward levels
   int nch_r;                      // metadata chunks of the row-by-row factorisation
   int n_flow, flow_levels;        // its wavefront tasks and their levels (0: chunks only)
+  int flow_waves;                 // wavefronts that take tasks
   int flow_meta;                  // words of a wavefront's task record area
   int flow_buf;                   // row buffer of a wavefront, in blocks of one scenario
   int nch_ut, nch_lt;             // metadata chunks of the transposed solves
@@ -158,13 +159,13 @@ constexpr int res_newton_threads() { return kResThreads; }
 inline int res_newton_threads(bool) { return kResThreads; }
 
 // slice = scenarios per workgroup: 1, 2 or 4 when LDS-resident, up to 16 otherwise.
-// rows: HBM-resident slices factor row by row (else by levels, one scenario per slice).
+// factor: of HBM-resident slices (by levels: one scenario per slice).
 hipError_t launch_newton(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds,
-                         bool lds_res, bool rows, hipStream_t st);
+                         bool lds_res, Factoring factor, hipStream_t st);
 // slice > 0: LDS-resident adjoint slices of that width (kResThreads threads);
 // slice < 0: HBM-resident slices of width -slice reading the forward solve's
 // slice workspace (at most 1024 threads)
-hipError_t launch_adjoint(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds, bool rows,
+hipError_t launch_adjoint(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds, Factoring factor,
                           hipStream_t st);
 hipError_t launch_jacobian_dense(const KParams& kp, int grid, hipStream_t st);
 // Step-2 recovery of the generation block for kp.count scenarios

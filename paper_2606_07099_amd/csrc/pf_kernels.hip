@@ -903,13 +903,17 @@ __device__ __forceinline__ void phase_rows(const Sym& m, const Dims& D, St<T>& c
 // Every wait ends: a task waits for earlier tasks only, tasks are taken in
 // order by resident wavefronts, and each of these finishes its task before it
 // waits in another, so the earliest unfinished task never waits.
-// lds: the record areas of the wavefronts, then the count of unfinished tasks
+// Where long rows need more LDS than all wavefronts can have, only the first
+// ones take tasks.  LONG: records beyond the three loads per lane; of its own,
+// since the loop costs the FP32 kernel 1 % where no record needs it (9241 buses
+// x256, mixed: 8.75 and 8.84 ms).
+// lds: the record areas of these wavefronts, then the count of unfinished tasks
 // per level, then the next task.
-template <typename T>
+template <typename T, bool LONG>
 __device__ __forceinline__ void phase_flow(const Sym& m, const Dims& D, St<T>& c, int tid, int nt, bool fwd,
                                            bool fill_only, int* piv, unsigned char* lds, T* buf) {
   constexpr int kAhead = 2;
-  const int nw = nt >> 6, wv = __builtin_amdgcn_readfirstlane(tid >> 6), ln = tid & 63;
+  const int nw = D.flow_waves, wv = __builtin_amdgcn_readfirstlane(tid >> 6), ln = tid & 63;
   int* left = reinterpret_cast<int*>(lds) + nw * D.flow_meta;
   int* next = left + D.flow_levels;
   for (int q = tid; q < D.flow_levels; q += nt) left[q] = m.fl_level[q];
@@ -929,7 +933,7 @@ __device__ __forceinline__ void phase_flow(const Sym& m, const Dims& D, St<T>& c
       cnt = m.fl_task[2 * t + 1];
     }
   };
-  take();
+  if (wv < nw) take();
   while (cnt) {
     {
       constexpr int kPre = kFlowMaxWords / 256;
@@ -941,6 +945,8 @@ __device__ __forceinline__ void phase_flow(const Sym& m, const Dims& D, St<T>& c
 #pragma unroll
       for (int u = 0; u < kPre; ++u)
         if (ln + 64 * u < cnt) rec[ln + 64 * u] = pre[u];
+      if (LONG)
+        for (int q = ln + 64 * kPre; q < cnt; q += 64) rec[q] = src[q];
     }
     take();   // the next task: its entry is loaded behind this one's work
     asm volatile("" ::: "memory");
@@ -1054,10 +1060,10 @@ __device__ __forceinline__ void phase_flow(const Sym& m, const Dims& D, St<T>& c
 }
 
 // the row-by-row factorisation of a slice
-template <typename T, int S>
+template <typename T, int S, bool LONG>
 __device__ __forceinline__ void factor_rows(const Sym& m, const Dims& D, St<T>& c, int tid, int nt, bool fwd,
                                             bool fill_only, int* piv, unsigned char* lds, T* buf) {
-  if constexpr (S == 1) phase_flow<T>(m, D, c, tid, nt, fwd, fill_only, piv, lds, buf);
+  if constexpr (S == 1) phase_flow<T, LONG>(m, D, c, tid, nt, fwd, fill_only, piv, lds, buf);
   else phase_rows<T, S>(m, D, c, tid, nt, fwd, fill_only, piv, lds, buf);
 }
 
@@ -1937,8 +1943,9 @@ __device__ __forceinline__ void phase_set_state(const Dims& D, St<T>& c, int tid
 // ----------------------------------------------------------------------------
 // the Newton kernel: one workgroup = one slice of S scenarios
 
-template <typename T, bool RES, int S, bool ROWS>
+template <typename T, bool RES, int S, int FACTOR>
 __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton(KParams kp) {
+  constexpr bool ROWS = FACTOR != FACTOR_LEVELS;
   static_assert(!(RES && ROWS), "row-by-row factorisation: HBM-resident slices");
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, nt = blockDim.x;
@@ -2046,7 +2053,7 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
     }
     if (kp.mode == MODE_EVAL_MISMATCH || kp.mode == MODE_EVAL_FACTOR) break;
     if (kp.mode == MODE_EVAL_FILL) {
-      if constexpr (ROWS) factor_rows<T, S>(m, D, c, tid, nt, false, true, piv, stg, tl);
+      if constexpr (ROWS) factor_rows<T, S, FACTOR == FACTOR_LONG_ROWS>(m, D, c, tid, nt, false, true, piv, stg, tl);
       else phase_fill<T, S, RES>(m, D, c, tid, nt);
       break;
     }
@@ -2057,7 +2064,7 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
     // dx in a streaming pass of its own
     pc.count(PH_NEWTON_STEPS);
     if constexpr (ROWS) {
-      factor_rows<T, S>(m, D, c, tid, nt, true, false, piv, stg, tl);
+      factor_rows<T, S, FACTOR == FACTOR_LONG_ROWS>(m, D, c, tid, nt, true, false, piv, stg, tl);
     } else {
       phase_fill<T, S, RES>(m, D, c, tid, nt);
       pc.mark(PH_FILL);
@@ -2229,7 +2236,7 @@ __global__ void __launch_bounds__(RES ? res_newton_threads<T>() : 1024) k_newton
   if (keep) {
     if (tid < S) piv[tid] = 0;
     if constexpr (ROWS) {
-      factor_rows<T, S>(m, D, c, tid, nt, false, false, piv, stg, tl);
+      factor_rows<T, S, FACTOR == FACTOR_LONG_ROWS>(m, D, c, tid, nt, false, false, piv, stg, tl);
     } else {
       phase_fill<T, S, RES>(m, D, c, tid, nt);
       phase_factor<T, S, RES>(m, D, c, tid, nt, gmin, false, piv, stg);
@@ -2897,26 +2904,29 @@ __global__ void __launch_bounds__(256) k_jacobian_dense(KParams kp) {
 
 template <typename T>
 static hipError_t launch_newton_t(const KParams& kp, int slice, int grid, int nt, size_t lds,
-                                  bool res, bool rows, hipStream_t st) {
+                                  bool res, Factoring factor, hipStream_t st) {
   dim3 g(grid), b(nt);
   if (res && (nt != res_newton_threads<T>() || slice > kResMaxSlice)) return hipErrorInvalidValue;
-  if (!res && !rows) {
+  if (!res && factor == FACTOR_LONG_ROWS) {
     if (slice != 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_newton<T, false, 1, false>), g, b, lds, st, kp);
+    hipLaunchKernelGGL((k_newton<T, false, 1, FACTOR_LONG_ROWS>), g, b, lds, st, kp);
+  } else if (!res && factor == FACTOR_LEVELS) {
+    if (slice != 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_newton<T, false, 1, FACTOR_LEVELS>), g, b, lds, st, kp);
   } else if (!res) {
     switch (slice) {
-      case 1: hipLaunchKernelGGL((k_newton<T, false, 1, true>), g, b, lds, st, kp); break;
-      case 2: hipLaunchKernelGGL((k_newton<T, false, 2, true>), g, b, lds, st, kp); break;
-      case 4: hipLaunchKernelGGL((k_newton<T, false, 4, true>), g, b, lds, st, kp); break;
-      case 8: hipLaunchKernelGGL((k_newton<T, false, 8, true>), g, b, lds, st, kp); break;
-      case 16: hipLaunchKernelGGL((k_newton<T, false, 16, true>), g, b, lds, st, kp); break;
+      case 1: hipLaunchKernelGGL((k_newton<T, false, 1, FACTOR_ROWS>), g, b, lds, st, kp); break;
+      case 2: hipLaunchKernelGGL((k_newton<T, false, 2, FACTOR_ROWS>), g, b, lds, st, kp); break;
+      case 4: hipLaunchKernelGGL((k_newton<T, false, 4, FACTOR_ROWS>), g, b, lds, st, kp); break;
+      case 8: hipLaunchKernelGGL((k_newton<T, false, 8, FACTOR_ROWS>), g, b, lds, st, kp); break;
+      case 16: hipLaunchKernelGGL((k_newton<T, false, 16, FACTOR_ROWS>), g, b, lds, st, kp); break;
       default: return hipErrorInvalidValue;
     }
   } else {
     switch (slice) {
-      case 1: hipLaunchKernelGGL((k_newton<T, true, 1, false>), g, b, lds, st, kp); break;
-      case 2: hipLaunchKernelGGL((k_newton<T, true, 2, false>), g, b, lds, st, kp); break;
-      case 4: hipLaunchKernelGGL((k_newton<T, true, 4, false>), g, b, lds, st, kp); break;
+      case 1: hipLaunchKernelGGL((k_newton<T, true, 1, FACTOR_LEVELS>), g, b, lds, st, kp); break;
+      case 2: hipLaunchKernelGGL((k_newton<T, true, 2, FACTOR_LEVELS>), g, b, lds, st, kp); break;
+      case 4: hipLaunchKernelGGL((k_newton<T, true, 4, FACTOR_LEVELS>), g, b, lds, st, kp); break;
       default: return hipErrorInvalidValue;
     }
   }
@@ -2924,19 +2934,19 @@ static hipError_t launch_newton_t(const KParams& kp, int slice, int grid, int nt
 }
 
 hipError_t launch_newton(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds,
-                         bool lds_res, bool rows, hipStream_t st) {
-  return fp32 ? launch_newton_t<float>(kp, slice, grid, nt, lds, lds_res, rows, st)
-              : launch_newton_t<double>(kp, slice, grid, nt, lds, lds_res, rows, st);
+                         bool lds_res, Factoring factor, hipStream_t st) {
+  return fp32 ? launch_newton_t<float>(kp, slice, grid, nt, lds, lds_res, factor, st)
+              : launch_newton_t<double>(kp, slice, grid, nt, lds, lds_res, factor, st);
 }
 
 template <typename T>
-static hipError_t launch_adjoint_hbm_t(const KParams& kp, int slice, int grid, int nt, size_t lds, bool rows,
+static hipError_t launch_adjoint_hbm_t(const KParams& kp, int slice, int grid, int nt, size_t lds, Factoring factor,
                                        hipStream_t st);
 
 template <typename T>
-static hipError_t launch_adjoint_t(const KParams& kp, int slice, int grid, int nt, size_t lds, bool rows,
+static hipError_t launch_adjoint_t(const KParams& kp, int slice, int grid, int nt, size_t lds, Factoring factor,
                                    hipStream_t st) {
-  if (slice < 0) return launch_adjoint_hbm_t<T>(kp, -slice, grid, nt, lds, rows, st);
+  if (slice < 0) return launch_adjoint_hbm_t<T>(kp, -slice, grid, nt, lds, factor, st);
   if (nt != kResThreads) return hipErrorInvalidValue;
   switch (slice) {
     case 1: hipLaunchKernelGGL((k_adjoint_slice<T, true, 1, false>), dim3(grid), dim3(nt), lds, st, kp); break;
@@ -2948,10 +2958,10 @@ static hipError_t launch_adjoint_t(const KParams& kp, int slice, int grid, int n
 }
 
 template <typename T>
-static hipError_t launch_adjoint_hbm_t(const KParams& kp, int slice, int grid, int nt, size_t lds, bool rows,
+static hipError_t launch_adjoint_hbm_t(const KParams& kp, int slice, int grid, int nt, size_t lds, Factoring factor,
                                        hipStream_t st) {
   if (nt > 1024) return hipErrorInvalidValue;
-  if (!rows) {
+  if (factor == FACTOR_LEVELS) {
     if (slice != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_adjoint_slice<T, false, 1, false>), dim3(grid), dim3(nt), lds, st, kp);
     return hipGetLastError();
@@ -2967,10 +2977,10 @@ static hipError_t launch_adjoint_hbm_t(const KParams& kp, int slice, int grid, i
   return hipGetLastError();
 }
 
-hipError_t launch_adjoint(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds, bool rows,
+hipError_t launch_adjoint(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds, Factoring factor,
                           hipStream_t st) {
-  return fp32 ? launch_adjoint_t<float>(kp, slice, grid, nt, lds, rows, st)
-              : launch_adjoint_t<double>(kp, slice, grid, nt, lds, rows, st);
+  return fp32 ? launch_adjoint_t<float>(kp, slice, grid, nt, lds, factor, st)
+              : launch_adjoint_t<double>(kp, slice, grid, nt, lds, factor, st);
 }
 
 hipError_t launch_recover(const KParams& kp, hipStream_t st) {
@@ -2992,15 +3002,16 @@ static hipError_t set_lds_t(int max_lds) {
     hipError_t r = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
     if (r != hipSuccess) e = r;
   };
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 1, false>));
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 1, true>));
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 2, true>));
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 4, true>));
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 8, true>));
-  set(reinterpret_cast<const void*>(&k_newton<T, false, 16, true>));
-  set(reinterpret_cast<const void*>(&k_newton<T, true, 1, false>));
-  set(reinterpret_cast<const void*>(&k_newton<T, true, 2, false>));
-  set(reinterpret_cast<const void*>(&k_newton<T, true, 4, false>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 1, FACTOR_LEVELS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 1, FACTOR_ROWS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 1, FACTOR_LONG_ROWS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 2, FACTOR_ROWS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 4, FACTOR_ROWS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 8, FACTOR_ROWS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 16, FACTOR_ROWS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, true, 1, FACTOR_LEVELS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, true, 2, FACTOR_LEVELS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, true, 4, FACTOR_LEVELS>));
   set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 1, false>));
   set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 2, false>));
   set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 4, false>));

@@ -162,6 +162,17 @@ int build_row_chunks(const Symbolic& S, const LuStorage& st, int32_t slice, int3
   return 0;
 }
 
+int32_t flow_row_words(const Symbolic& S) {
+  int32_t most = 0;
+  for (int32_t a = 0; a < S.nb; ++a) {
+    const int32_t end = a < S.tail_base ? S.diag[a] : S.tail_split[a - S.tail_base];
+    int64_t targets = 0;
+    for (int32_t p = S.rp[a]; p < end; ++p) targets += S.rp[S.ci[p] + 1] - S.diag[S.ci[p]] - 1;
+    most = (int32_t)std::max<int64_t>(most, 12 + 4 * (int64_t)(end - S.rp[a]) + (targets + 15) / 16 * 4);
+  }
+  return most;
+}
+
 int build_flow_tasks(const Symbolic& S, const LuStorage& st, int32_t waves, int64_t buffer_blocks,
                      int32_t budget_ints, FlowTasks& out, std::string& err) {
   out = FlowTasks{};

@@ -203,7 +203,7 @@ int build_row_chunks(const Symbolic& S, const LuStorage& st, int32_t slice, int3
 //  pivot's U part, first target}, targets (blocks of the row, one byte each).
 constexpr int32_t kFlowMaxRow = 255;       // blocks of a row (one-byte targets)
 constexpr int32_t kFlowMaxLevels = 1024;   // levels counted in LDS
-constexpr int32_t kFlowMaxWords = 768;     // words of a record (three 16-byte loads per lane)
+constexpr int32_t kFlowMaxWords = 768;     // words of a record of several rows (three 16-byte loads per lane)
 struct FlowTasks {
   std::vector<int32_t> task;      // [tasks][2]: first word of its record, 16-byte words of it
   std::vector<int32_t> blob;      // the records
@@ -216,6 +216,8 @@ struct FlowTasks {
 // when a row or the levels do not fit.
 int build_flow_tasks(const Symbolic& S, const LuStorage& st, int32_t waves, int64_t buffer_blocks,
                      int32_t budget_ints, FlowTasks& out, std::string& err);
+// words of the longest record of a single row
+int32_t flow_row_words(const Symbolic& S);
 
 // Returns 0 on success; on failure a negative PF_E* code and a message.
 // tail_max: largest dense tail (0 disables it; at most 64); tail_level: most

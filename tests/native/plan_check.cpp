@@ -216,12 +216,15 @@ int main(int argc, char** argv) {
   const size_t end = P.tail_off + P.area;
   CHECK(P.y_bytes == 0 ? P.y_off == 0 : P.y_off % 16 == 0 && P.y_off >= end && P.y_bytes >= 2 * (size_t)S.nb * P.slice * tsz, "y");
   CHECK(P.lds_bytes >= std::max(end, P.y_off + P.y_bytes) && P.lds_bytes <= shape.max_lds, "%zu bytes of LDS", P.lds_bytes);
-  const char* path = P.rows ? P.slice == 1 ? "tasks" : "rows" : "levels";
-  if (P.rows) {
+  const bool rows = P.factor != FACTOR_LEVELS;
+  const char* path = rows ? P.slice == 1 ? "tasks" : "rows" : "levels";
+  CHECK((P.factor == FACTOR_LONG_ROWS) == (P.flow.max_ints > kFlowMaxWords), "long records: %d words", P.flow.max_ints);
+  if (rows) {
     Replay R(S, P.st);
     if (P.slice == 1) {
-      CHECK((size_t)waves * P.flow_buf * 4 * tsz <= P.area, "row buffers beyond their area");
-      replay_tasks(R, P, waves);
+      CHECK(P.flow_waves >= 1 && P.flow_waves <= waves, "%d wavefronts take tasks", P.flow_waves);
+      CHECK((size_t)P.flow_waves * P.flow_buf * 4 * tsz <= P.area, "row buffers beyond their area");
+      replay_tasks(R, P, P.flow_waves);
     } else {
       replay_rows(R, P, shape.threads, tsz);
     }
@@ -229,7 +232,7 @@ int main(int argc, char** argv) {
   } else {
     CHECK(!P.chunks.f_ptr.empty(), "no factor tasks");
   }
-  std::printf("path %s slice %d y %zu lds %zu tail %d longest %d words %d violations %d\n", path, P.slice, P.y_bytes,
-              P.lds_bytes, S.tail_t, S.max_row_blocks, P.flow.max_ints, g_fail);
+  std::printf("path %s slice %d y %zu lds %zu tail %d longest %d words %d waves %d violations %d\n", path, P.slice, P.y_bytes,
+              P.lds_bytes, S.tail_t, S.max_row_blocks, P.flow.max_ints, P.flow_waves, g_fail);
   return g_fail ? 1 : 0;
 }

@@ -1,0 +1,25 @@
+"""Networks with long rows on the HBM-resident paths, against the dense oracle:
+a row whose task record and buffer take the share of several wavefronts, so that
+only some of them take tasks, with wide and narrow workgroups."""
+import numpy as np
+import pytest
+
+from test_gpu_rows import _check
+from test_host_plan import hubs
+from gen.grids import Scenarios
+
+pytestmark = pytest.mark.gpu
+
+
+def _scenarios(net, batch, seed=3):
+    rng = np.random.default_rng(seed)
+    pq = np.asarray(net.bus_type) == 0
+    pd = np.where(pq, rng.uniform(1e-5, 2e-5, (batch, net.n_bus)), 0.0)
+    return Scenarios(pd, 0.3 * pd, np.zeros_like(pd), np.ones_like(pd))
+
+
+@pytest.mark.parametrize("leaves", [150, 200, 235])
+def test_long_rows_as_tasks_match_the_oracle(leaves, device):
+    net = hubs(300, leaves)
+    sc = _scenarios(net, 20)
+    _check(net, sc, 1e-9, "fp64", device, (0, 19), 1)

@@ -6,9 +6,10 @@ import re
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
-from gen.grids import GridSpec, make_network
+from gen.grids import GridSpec, Network, make_network
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_07099_amd", "csrc")
@@ -33,6 +34,21 @@ def grid(n, seed=1):
                         seed)
 
 
+def hubs(n, leaves):
+    """A ring of n buses, ``leaves`` more at each of two of them: rows as long as
+    that, whose task records have a step per leaf."""
+    ring = np.arange(n)
+    f = np.concatenate([ring, np.repeat([5, n // 2], leaves)])
+    t = np.concatenate([(ring + 1) % n, n + np.arange(2 * leaves)])
+    m = n + 2 * leaves
+    bt = np.where(np.arange(m) % 7 == 3, 1, 0)
+    bt[n:] = 0
+    bt[0] = 2
+    r = np.full(f.size, 0.01)
+    return Network("hubs", m, bt.astype(np.int32), f.astype(np.int32), t.astype(np.int32), r, 5 * r,
+                   np.zeros(f.size), np.ones(m), np.zeros(m), np.zeros(m))
+
+
 def write(path, net):
     with open(path, "w") as fh:
         fh.write(f"{net.n_bus} {len(net.f)}\n" + " ".join(str(int(v)) for v in net.bus_type) + "\n")
@@ -45,11 +61,28 @@ def plan(checker, path, precision="fp64", batch=256, threads=1024):
     r = subprocess.run([checker, path, precision, str(batch), str(threads)], capture_output=True, text=True,
                        timeout=600)
     assert r.returncode == 0 and "violations 0" in r.stdout, r.stdout + r.stderr
-    m = re.search(r"path (\w+) slice (\d+) y (\d+) lds (\d+) tail (\d+) longest (\d+) words (\d+)", r.stdout)
-    return dict(zip(("slice", "y", "lds", "tail", "longest", "words"), map(int, m.groups()[1:])), path=m.group(1))
+    m = re.search(r"path (\w+) slice (\d+) y (\d+) lds (\d+) tail (\d+) longest (\d+) words (\d+) waves (\d+)", r.stdout)
+    return dict(zip(("slice", "y", "lds", "tail", "longest", "words", "waves"), map(int, m.groups()[1:])), path=m.group(1))
 
 
 @pytest.mark.parametrize("n", [300, 1354, 2600, 4200, 4600, 5000, 5600, 6000, 6600])
 def test_single_scenario_fp64_slices_factor_as_tasks(checker, tmp_path, n):
     """y in LDS does not crowd out the wavefronts' row buffers."""
     assert plan(checker, write(tmp_path / "net.txt", grid(n)))["path"] == "tasks"
+
+
+@pytest.mark.parametrize("leaves,words,waves", [(150, 650, 16), (200, 850, 8), (235, 1000, 8)])
+def test_a_long_row_keeps_the_tasks(checker, tmp_path, leaves, words, waves):
+    """A record beyond a wavefront's share of the metadata, and a row beyond its
+    share of the buffers."""
+    p = plan(checker, write(tmp_path / "net.txt", hubs(400, leaves)))
+    assert p["path"] == "tasks" and p["longest"] > leaves and p["words"] > words and p["waves"] == waves
+    # beyond one-byte targets: by levels
+    assert plan(checker, write(tmp_path / "net.txt", hubs(400, 256)))["path"] == "levels"
+
+
+def test_a_record_of_the_full_share_keeps_the_tasks(checker, tmp_path):
+    """9000 buses whose longest record is a few words more than a sixteenth of
+    the metadata area."""
+    p = plan(checker, write(tmp_path / "net.txt", grid(9000, seed=2)))
+    assert p["path"] == "tasks" and p["waves"] == 16
