@@ -74,6 +74,12 @@ extern "C" {
                                    scalar pivots is <= eps * |row of the block| (eps = 1e-14
                                    for FP64 factors, 1e-7 for FP32) or its inverse is not finite */
 
+/* how a template factors (pf_template_factor_path) */
+#define PF_FACTOR_LDS 0     /* LDS-resident slices, by levels */
+#define PF_FACTOR_LEVELS 1  /* HBM-resident slices, by levels in place */
+#define PF_FACTOR_ROWS 2    /* HBM-resident slices of several scenarios, row by row */
+#define PF_FACTOR_TASKS 3   /* HBM-resident slices of one scenario, row by row as wavefront tasks */
+
 typedef struct pf_template pf_template; /* opaque */
 
 typedef struct {
@@ -157,6 +163,10 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
 
 /* Sizes of the analysis.  Host-only, never touches the device. */
 int pf_template_info(const pf_template* tpl, pf_template_stats* out);
+
+/* How the template's solves factor J1: *path receives a PF_FACTOR_* value.
+   Host-only.  Errors: PF_EINVAL. */
+int pf_template_factor_path(const pf_template* tpl, int32_t* path);
 
 /* The 2x2-block pattern of L+U in the library's storage order (one-time
    symbolic analysis, Sec. III-B): host outputs row_bus[nnzb_lu] and

@@ -848,6 +848,15 @@ int pf_debug_phase_clocks(uint64_t* ticks, int32_t n, int32_t reset, double* tic
   return PF_OK;
 }
 
+int pf_template_factor_path(const pf_template* t, int32_t* path) {
+  g_err.clear();
+  if (!t || !path) return fail(PF_EINVAL, "pf_template_factor_path: NULL argument");
+  if (t->lds_res) *path = PF_FACTOR_LDS;
+  else if (t->factor == sable::FACTOR_LEVELS) *path = PF_FACTOR_LEVELS;
+  else *path = t->slice == 1 ? PF_FACTOR_TASKS : PF_FACTOR_ROWS;
+  return PF_OK;
+}
+
 int pf_template_block_pattern(const pf_template* t, int32_t* row_bus, int32_t* col_bus) {
   g_err.clear();
   if (!t || !row_bus || !col_bus) return fail(PF_EINVAL, "pf_template_block_pattern: NULL argument");

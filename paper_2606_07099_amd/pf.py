@@ -11,7 +11,7 @@ import ctypes
 import numpy as np
 
 from . import _lib
-from ._lib import (PFError, PFOptions, PFStats, check, lib, PF_FP64, PF_MIXED, PF_EVAL_ADJOINT,
+from ._lib import (FACTOR_PATHS, PFError, PFOptions, PFStats, check, lib, PF_FP64, PF_MIXED, PF_EVAL_ADJOINT,
                    PF_EVAL_FILL, PF_EVAL_JACOBIAN, PF_EVAL_MISMATCH, PF_EVAL_STEP, PF_OP_BASE, PF_OP_J1,
                    PF_OP_J1T, PF_OP_J2T, PF_OP_J3T)
 
@@ -143,7 +143,9 @@ class PFTemplate:
     def info(self) -> dict:
         st = PFStats()
         check(lib().pf_template_info(self._h, ctypes.byref(st)))
-        return st.as_dict()
+        path = ctypes.c_int32()
+        check(lib().pf_template_factor_path(self._h, ctypes.byref(path)))
+        return {**st.as_dict(), "factor_path": FACTOR_PATHS[path.value]}
 
     @property
     def n_j(self) -> int:

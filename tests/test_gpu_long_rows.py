@@ -23,3 +23,15 @@ def test_long_rows_as_tasks_match_the_oracle(leaves, device):
     net = hubs(300, leaves)
     sc = _scenarios(net, 20)
     _check(net, sc, 1e-9, "fp64", device, (0, 19), 1)
+
+
+def test_the_template_tells_its_path(device):
+    from paper_2606_07099_amd import PFTemplate
+    from gen.grids import SPECS, make_network
+    c0 = make_network(SPECS["c0"])
+    for net, batch, precision, path in ((c0, 4, "fp64", "lds"), (hubs(300, 235), 20, "fp64", "tasks"),
+                                        (hubs(300, 256), 20, "fp64", "levels"),
+                                        (hubs(900, 20), 20, "mixed", "levels"), (hubs(900, 20), 4200, "fp64", "rows")):
+        tpl = PFTemplate.from_network(net, batch, precision=precision)
+        assert tpl.info()["factor_path"] == path
+        tpl.close()
