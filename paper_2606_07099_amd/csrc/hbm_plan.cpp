@@ -39,18 +39,18 @@ int plan_slice(const Symbolic& S, const HbmShape& h, bool rows, bool want_y, int
   // the tail's update words are staged in the metadata area (free while the
   // tail is factored) when the area, grown within the room, holds them
   p.tail_prog_lds = (upd_words + 3) / 4 * 16 <= room;
-  p.chunk_ints = std::max<int>(p.chunks.max_ints, p.tail_prog_lds ? (int)(upd_words + 3) / 4 * 4 : 0);
+  const int solve_ints = std::max<int>(p.chunks.max_ints, p.tail_prog_lds ? (int)(upd_words + 3) / 4 * 4 : 0);
+  p.chunk_ints = solve_ints;
   p.row_chunks = RowChunks{};
   p.flow = FlowTasks{};
   p.area = tail_bytes;
   p.factor = rows ? FACTOR_ROWS : FACTOR_LEVELS;
   if (rows) {
     p.chunk_ints = std::max(p.chunk_ints, budget);
+    const int counts = (S.n_fs_levels + 2 + 3) / 4 * 4;   // wavefront tasks: the levels' counts and the next task
     if (sl == 1) {
-      // wavefront tasks, each wavefront with its share of the metadata area,
-      // behind which the levels are counted, and of the buffers.  A long row's
-      // record takes more than that share, out of what the buffers would have.
-      const int counts = (S.n_fs_levels + 2 + 3) / 4 * 4;
+      // each wavefront has its share of the metadata area and of the buffers.
+      // A long row's record takes more than that, out of what the buffers would have.
       p.flow_waves = waves;
       p.flow_meta = std::min<int>(kFlowMaxWords, std::max(0, p.chunk_ints - counts) / waves / 4 * 4);
       p.flow_meta = std::max(p.flow_meta, flow_row_words(S));
@@ -69,6 +69,19 @@ int plan_slice(const Symbolic& S, const HbmShape& h, bool rows, bool want_y, int
       rc = build_row_chunks(S, p.st, sl, h.threads, (int64_t)(p.area / (4 * tsz * sl)), budget, p.row_chunks, err);
     }
     if (rc != 0) return rc;
+    // and no more of it than the schedule takes, so that several of the smaller
+    // workgroups that block_threads selects share a compute unit (300 buses x1000,
+    // FP64, 128 threads: 0.70 ms with 39 KB per workgroup, 1.08 with all 160; with
+    // 1024 threads the registers leave room for one)
+    if (sl == 1) {
+      p.flow_meta = p.flow.max_ints;
+      p.flow_buf = p.flow.max_buffer;
+      p.chunk_ints = std::max(solve_ints, counts + waves * p.flow_meta);
+      p.area = std::max(tail_bytes, (size_t)waves * p.flow_buf * 4 * tsz);
+    } else {
+      p.chunk_ints = std::max(solve_ints, p.row_chunks.max_ints);
+      p.area = std::max(tail_bytes, (size_t)p.row_chunks.max_buffer * 4 * tsz * sl);
+    }
   }
   p.tail_off = fixed + 4 * (size_t)p.chunk_ints;
   p.lds_bytes = (p.tail_off + p.area + 15) / 16 * 16;

@@ -614,8 +614,8 @@ int pf_template_build(int32_t n_bus, const int32_t* bus_type, const int32_t* y_i
     bsl = sd + stt;
   }
   he = hipMemset(t->ws_i, 0xff, bi);
-  if (he == hipSuccess && std::max(t->lds_bytes, t->adj_lds) > 64 * 1024)
-    he = sable::set_lds_limits(std::max(t->lds_bytes, t->adj_lds));
+  // the device's own limit, so that no template lowers another's
+  if (he == hipSuccess && std::max(t->lds_bytes, t->adj_lds) > 64 * 1024) he = sable::set_lds_limits(max_lds);
   if (he == hipSuccess) he = sable::set_operator_lds(S.n_bus);
   if (he == hipSuccess) he = hipDeviceSynchronize();
   if (he != hipSuccess) { pf_template_destroy(t); return hip_fail(he, "pf_template_build: set-up"); }

@@ -231,6 +231,7 @@ int build_flow_tasks(const Symbolic& S, const LuStorage& st, int32_t waves, int6
         off += len(a);
         most = std::max(most, steps(a));
       }
+      out.max_buffer = std::max(out.max_buffer, off);
       std::vector<int32_t> c = {(int32_t)(r1 - r0), lg, h, most};
       c.insert(c.end(), rec.begin(), rec.end());
       c.insert(c.end(), stp.begin(), stp.end());

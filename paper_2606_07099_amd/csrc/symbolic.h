@@ -209,6 +209,7 @@ struct FlowTasks {
   std::vector<int32_t> blob;      // the records
   std::vector<int32_t> per_level; // [levels] tasks
   int32_t max_ints = 0;           // longest record
+  int32_t max_buffer = 0;         // most blocks of a task
   int32_t n_tasks() const { return (int32_t)task.size() / 2; }
 };
 // waves: wavefronts of the workgroup; buffer_blocks: row buffer of a wavefront;

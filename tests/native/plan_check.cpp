@@ -214,6 +214,11 @@ int main(int argc, char** argv) {
   CHECK(P.tail_off % 16 == 0 && P.tail_off >= kScratchBytes + 4 * (size_t)P.chunk_ints + prefix, "row buffers overlap");
   CHECK(P.area >= tail_copy_bytes(S, P.slice, shape.fp32), "the tail copy does not fit");
   const size_t end = P.tail_off + P.area;
+  // no more LDS than the schedule takes
+  const int counts = (int)P.flow.per_level.size() ? (S.n_fs_levels + 2 + 3) / 4 * 4 : 0;
+  const int solve_ints = std::max(P.chunks.max_ints, P.tail_prog_lds ? ((int)S.tail_prog.size() - S.tail_prog_prefix + 3) / 4 * 4 : 0);
+  CHECK(P.chunk_ints == std::max({solve_ints, P.row_chunks.max_ints, counts + P.flow_waves * P.flow.max_ints}), "%d words of metadata area", P.chunk_ints);
+  CHECK(P.area == std::max({tail_copy_bytes(S, P.slice, shape.fp32), (size_t)P.row_chunks.max_buffer * 4 * tsz * P.slice, (size_t)P.flow_waves * P.flow.max_buffer * 4 * tsz}), "%zu bytes of row buffers", P.area);
   CHECK(P.y_bytes == 0 ? P.y_off == 0 : P.y_off % 16 == 0 && P.y_off >= end && P.y_bytes >= 2 * (size_t)S.nb * P.slice * tsz, "y");
   CHECK(P.lds_bytes >= std::max(end, P.y_off + P.y_bytes) && P.lds_bytes <= shape.max_lds, "%zu bytes of LDS", P.lds_bytes);
   const bool rows = P.factor != FACTOR_LEVELS;

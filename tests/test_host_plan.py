@@ -86,3 +86,12 @@ def test_a_record_of_the_full_share_keeps_the_tasks(checker, tmp_path):
     the metadata area."""
     p = plan(checker, write(tmp_path / "net.txt", grid(9000, seed=2)))
     assert p["path"] == "tasks" and p["waves"] == 16
+
+
+@pytest.mark.parametrize("n,precision,batch", [(300, "fp64", 1000), (300, "mixed", 2400), (118, "fp64", 400),
+                                               (1354, "fp64", 2400), (1354, "fp64", 400)])
+@pytest.mark.parametrize("threads", [64, 256, 512])
+def test_narrow_workgroups_take_the_lds_they_use(checker, tmp_path, n, precision, batch, threads):
+    p = plan(checker, write(tmp_path / "net.txt", grid(n)), precision, batch, threads)
+    if threads == 64 and n <= 300 and p["slice"] <= 2:   # several of them fit a compute unit
+        assert 3 * p["lds"] <= 160 * 1024
