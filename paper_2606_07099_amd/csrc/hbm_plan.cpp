@@ -9,6 +9,13 @@ namespace sable {
 
 namespace {
 
+// least metadata budget (int32 words)
+constexpr int32_t kMinChunkInts = 2048;
+
+// LDS before the row buffers / the tail copy besides the metadata: the kernels'
+// scratch and the tail program's solve prefix
+size_t fixed_bytes(const Symbolic& S) { return kScratchBytes + (4 * (size_t)S.tail_prog_prefix + 15) / 16 * 16; }
+
 // the plan for slices of p.slice scenarios that factor row by row (rows) or by
 // levels in place, with y in LDS where that leaves the full metadata budget (if
 // want_y); waves: wavefronts that take tasks (rows of one scenario)
@@ -17,13 +24,12 @@ int plan_slice(const Symbolic& S, const HbmShape& h, bool rows, bool want_y, int
   const int sl = p.slice;
   const size_t tsz = h.fp32 ? 4 : 8;
   const size_t upd_words = S.tail_prog.size() - (size_t)S.tail_prog_prefix;
-  const size_t prefix_bytes = (4 * (size_t)S.tail_prog_prefix + 15) / 16 * 16;
-  const size_t fixed = kScratchBytes + prefix_bytes;
+  const size_t fixed = fixed_bytes(S);
   const size_t tail_bytes = tail_copy_bytes(S, sl, h.fp32);
   // what the metadata can have beside the tail copy (S > 1: at most half of it
   // where rows need buffers) and, when that leaves the full metadata budget,
   // beside y: every solve's gathers then stay on chip
-  if (fixed + tail_bytes + 4 * 2048 > h.max_lds) {
+  if (fixed + tail_bytes + 4 * kMinChunkInts > h.max_lds) {
     err = "pf_template_build: the dense tail does not fit in LDS";
     return PF_EINVAL;
   }
@@ -97,13 +103,19 @@ int plan_hbm(const Symbolic& S, const HbmShape& h, HbmPlan& p, std::string& err)
   // per compute unit and leaves room in LDS for the tail copy and for staged
   // metadata; S = 1 always fits: the tail holds at most 32 x 32 blocks.  The
   // rows of the row-by-row factorisation have to fit beside the metadata too
-  // (in the place of the tail copy, which is made after it); where they do not,
-  // y gives way to them, and then some of the wavefronts that take tasks.  With
-  // FP32 factors neither does: the refinement solves, which y in LDS is for, are
-  // the larger part (11000 buses, mixed: x250 9.8 ms by levels, 10.2 by tasks
+  // (in the place of the tail copy, which is made after it).  Where they do not,
+  // y gives way to them, and with S = 1 some of the wavefronts that take tasks.
+  // With FP32 factors neither does: the refinement solves, which y in LDS is for,
+  // are the larger part (11000 buses, mixed: x250 9.8 ms by levels, 10.2 by tasks
   // without y, 9.8 by half as many wavefronts, x37 7.0 and 8.1; FP64 x250 10.6
-  // by levels, 6.8 by tasks without y).  A network whose rows do not fit even
-  // with S = 1 (more than 255 blocks) factors by levels in place.
+  // by levels, 6.8 by tasks without y).
+  // Rows that are too long for S scenarios may still fit half as many; beyond
+  // that the slice keeps its width and factors by levels in place (FP64 x4200, a
+  // hub of 400 leaves: 2.27 ms by levels of 16 scenarios, 1.92 by rows of 8, 2.62
+  // of 4; of 1000 leaves: 6.4 and, by rows of 2, 10.3; of 2000 leaves by levels of
+  // 16 and of one scenario: 18.9 and 75).  Only FP64 slices of two go to one: the
+  // width that tests/test_gpu_rows.py pins for a star of 2000 leaves x520,
+  // although two by levels would be faster (x600: 10.4 against 13.0 ms).
   p = HbmPlan{};
   while (p.slice < kMaxSlice && h.batch / (2 * p.slice) >= h.n_cu) p.slice *= 2;
   // Slices of one scenario with FP32 factors factor by levels in place on the
@@ -112,20 +124,22 @@ int plan_hbm(const Symbolic& S, const HbmShape& h, HbmPlan& p, std::string& err)
   // 300 buses x250, FP64: 0.36 and 0.34; 9241 buses x256, mixed: 9.4 and 8.8,
   // FP64 9.6 and 6.5).
   const bool by_levels = h.fp32 && S.nb < 4096;
-  int rc = PF_EINVAL;
-  for (;; p.slice /= 2) {
-    if (p.slice > 1 || !by_levels) {
-      int waves = h.threads / 64;
-      if ((rc = plan_slice(S, h, true, true, waves, p, err)) == 0) return 0;
-      if (!h.fp32) {
-        if ((rc = plan_slice(S, h, true, false, waves, p, err)) == 0) return 0;
-        while (p.slice == 1 && waves > 1)
-          if ((rc = plan_slice(S, h, true, false, waves /= 2, p, err)) == 0) return 0;
-      }
-    }
-    if (p.slice == 1) break;
-  }
-  return plan_slice(S, h, false, true, 0, p, err);
+  while (p.slice > 1 && fixed_bytes(S) + tail_copy_bytes(S, p.slice, h.fp32) + 4 * kMinChunkInts > h.max_lds) p.slice /= 2;
+  const int width = p.slice;
+  auto rows_fit = [&](int slice) {
+    p.slice = slice;
+    int waves = h.threads / 64;
+    if (plan_slice(S, h, true, true, waves, p, err) == 0) return true;
+    if (h.fp32) return false;
+    if (plan_slice(S, h, true, false, waves, p, err) == 0) return true;
+    while (slice == 1 && waves > 1)
+      if (plan_slice(S, h, true, false, waves /= 2, p, err) == 0) return true;
+    return false;
+  };
+  if (width > 1 ? rows_fit(width) || (width > 2 && rows_fit(width / 2)) : !by_levels && rows_fit(1)) return 0;
+  for (p.slice = width > 2 || h.fp32 ? width : 1; p.slice >= 1; p.slice /= 2)
+    if (plan_slice(S, h, false, true, 0, p, err) == 0) return 0;
+  return PF_EINVAL;
 }
 
 }  // namespace sable

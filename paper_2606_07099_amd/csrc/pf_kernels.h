@@ -159,7 +159,7 @@ constexpr int res_newton_threads() { return kResThreads; }
 inline int res_newton_threads(bool) { return kResThreads; }
 
 // slice = scenarios per workgroup: 1, 2 or 4 when LDS-resident, up to 16 otherwise.
-// factor: of HBM-resident slices (by levels: one scenario per slice).
+// factor: of HBM-resident slices.
 hipError_t launch_newton(const KParams& kp, bool fp32, int slice, int grid, int nt, size_t lds,
                          bool lds_res, Factoring factor, hipStream_t st);
 // slice > 0: LDS-resident adjoint slices of that width (kResThreads threads);

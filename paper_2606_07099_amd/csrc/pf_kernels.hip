@@ -2911,8 +2911,14 @@ static hipError_t launch_newton_t(const KParams& kp, int slice, int grid, int nt
     if (slice != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_newton<T, false, 1, FACTOR_LONG_ROWS>), g, b, lds, st, kp);
   } else if (!res && factor == FACTOR_LEVELS) {
-    if (slice != 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_newton<T, false, 1, FACTOR_LEVELS>), g, b, lds, st, kp);
+    switch (slice) {
+      case 1: hipLaunchKernelGGL((k_newton<T, false, 1, FACTOR_LEVELS>), g, b, lds, st, kp); break;
+      case 2: hipLaunchKernelGGL((k_newton<T, false, 2, FACTOR_LEVELS>), g, b, lds, st, kp); break;
+      case 4: hipLaunchKernelGGL((k_newton<T, false, 4, FACTOR_LEVELS>), g, b, lds, st, kp); break;
+      case 8: hipLaunchKernelGGL((k_newton<T, false, 8, FACTOR_LEVELS>), g, b, lds, st, kp); break;
+      case 16: hipLaunchKernelGGL((k_newton<T, false, 16, FACTOR_LEVELS>), g, b, lds, st, kp); break;
+      default: return hipErrorInvalidValue;
+    }
   } else if (!res) {
     switch (slice) {
       case 1: hipLaunchKernelGGL((k_newton<T, false, 1, FACTOR_ROWS>), g, b, lds, st, kp); break;
@@ -2962,8 +2968,14 @@ static hipError_t launch_adjoint_hbm_t(const KParams& kp, int slice, int grid, i
                                        hipStream_t st) {
   if (nt > 1024) return hipErrorInvalidValue;
   if (factor == FACTOR_LEVELS) {
-    if (slice != 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_adjoint_slice<T, false, 1, false>), dim3(grid), dim3(nt), lds, st, kp);
+    switch (slice) {
+      case 1: hipLaunchKernelGGL((k_adjoint_slice<T, false, 1, false>), dim3(grid), dim3(nt), lds, st, kp); break;
+      case 2: hipLaunchKernelGGL((k_adjoint_slice<T, false, 2, false>), dim3(grid), dim3(nt), lds, st, kp); break;
+      case 4: hipLaunchKernelGGL((k_adjoint_slice<T, false, 4, false>), dim3(grid), dim3(nt), lds, st, kp); break;
+      case 8: hipLaunchKernelGGL((k_adjoint_slice<T, false, 8, false>), dim3(grid), dim3(nt), lds, st, kp); break;
+      case 16: hipLaunchKernelGGL((k_adjoint_slice<T, false, 16, false>), dim3(grid), dim3(nt), lds, st, kp); break;
+      default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
   }
   switch (slice) {
@@ -3003,6 +3015,10 @@ static hipError_t set_lds_t(int max_lds) {
     if (r != hipSuccess) e = r;
   };
   set(reinterpret_cast<const void*>(&k_newton<T, false, 1, FACTOR_LEVELS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 2, FACTOR_LEVELS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 4, FACTOR_LEVELS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 8, FACTOR_LEVELS>));
+  set(reinterpret_cast<const void*>(&k_newton<T, false, 16, FACTOR_LEVELS>));
   set(reinterpret_cast<const void*>(&k_newton<T, false, 1, FACTOR_ROWS>));
   set(reinterpret_cast<const void*>(&k_newton<T, false, 1, FACTOR_LONG_ROWS>));
   set(reinterpret_cast<const void*>(&k_newton<T, false, 2, FACTOR_ROWS>));
@@ -3016,6 +3032,10 @@ static hipError_t set_lds_t(int max_lds) {
   set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 2, false>));
   set(reinterpret_cast<const void*>(&k_adjoint_slice<T, true, 4, false>));
   set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 1, false>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 2, false>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 4, false>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 8, false>));
+  set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 16, false>));
   set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 1, true>));
   set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 2, true>));
   set(reinterpret_cast<const void*>(&k_adjoint_slice<T, false, 4, true>));

@@ -35,3 +35,13 @@ def test_the_template_tells_its_path(device):
         tpl = PFTemplate.from_network(net, batch, precision=precision)
         assert tpl.info()["factor_path"] == path
         tpl.close()
+
+
+@pytest.mark.parametrize("batch,slice_width", [(1030, 4), (2050, 8), (4100, 16)])
+def test_wide_slices_by_levels_match_the_oracle(batch, slice_width, device):
+    """A hub's row of 2000 blocks fits no row chunk: the slice keeps its width
+    and factors by levels in place.  (FP64 only: with FP32 factors the gradient of
+    such a network is good to 3e-4, on every path.)"""
+    net = hubs(20, 2000, 1)
+    sc = _scenarios(net, batch)
+    _check(net, sc, 1e-9, "fp64", device, (batch - 1,), slice_width)

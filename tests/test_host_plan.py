@@ -34,13 +34,13 @@ def grid(n, seed=1):
                         seed)
 
 
-def hubs(n, leaves):
-    """A ring of n buses, ``leaves`` more at each of two of them: rows as long as
-    that, whose task records have a step per leaf."""
+def hubs(n, leaves, count=2):
+    """A ring of n buses, ``leaves`` more at each of one or two of them: rows as
+    long as that, whose task records have a step per leaf."""
     ring = np.arange(n)
-    f = np.concatenate([ring, np.repeat([5, n // 2], leaves)])
-    t = np.concatenate([(ring + 1) % n, n + np.arange(2 * leaves)])
-    m = n + 2 * leaves
+    f = np.concatenate([ring, np.repeat([5, n // 2][:count], leaves)])
+    t = np.concatenate([(ring + 1) % n, n + np.arange(count * leaves)])
+    m = n + count * leaves
     bt = np.where(np.arange(m) % 7 == 3, 1, 0)
     bt[n:] = 0
     bt[0] = 2
@@ -95,3 +95,20 @@ def test_narrow_workgroups_take_the_lds_they_use(checker, tmp_path, n, precision
     p = plan(checker, write(tmp_path / "net.txt", grid(n)), precision, batch, threads)
     if threads == 64 and n <= 300 and p["slice"] <= 2:   # several of them fit a compute unit
         assert 3 * p["lds"] <= 160 * 1024
+
+
+@pytest.mark.parametrize("precision,batch,slice_width",
+                         [("mixed", 600, 2), *((p, *x) for p in ("fp64", "mixed")
+                                               for x in ((1100, 4), (2100, 8), (4200, 16)))])
+def test_rows_that_do_not_fit_leave_the_slice_its_width(checker, tmp_path, precision, batch, slice_width):
+    p = plan(checker, write(tmp_path / "net.txt", hubs(20, 2000, 1)), precision, batch)
+    assert p["path"] == "levels" and p["slice"] == slice_width
+
+
+def test_rows_that_fit_half_the_slice_halve_it(checker, tmp_path):
+    path = write(tmp_path / "net.txt", hubs(20, 400, 1))
+    p = plan(checker, path, "fp64", 4200)
+    assert p["path"] == "rows" and p["slice"] == 8
+    # with y in device memory they fit the whole of a narrower one
+    p = plan(checker, path, "fp64", 2100)
+    assert p["path"] == "rows" and p["slice"] == 8 and p["y"] == 0
