@@ -96,6 +96,39 @@ int plan_slice(const Symbolic& S, const HbmShape& h, bool rows, bool want_y, int
   return 0;
 }
 
+// Whether slices of this many scenarios rather factor row by row than by levels.
+// The rows move fewer bytes, the levels have more lanes at work and wait less on
+// one row after the other (solves below in ms, by rows / by levels, with 1024
+// threads and the batches that give this width).
+bool prefer_rows(const Symbolic& S, const HbmShape& h, int slice) {
+  const size_t tsz = h.fp32 ? 4 : 8;
+  if (slice > 1) {
+    // Levels while the factors of one slice per compute unit stay well inside
+    // the 256 MB Infinity Cache, and one value of all scenarios of a block is
+    // short of a 64-byte run.  FP64 slices of two: 300 buses 0.78 / 0.68, 1354
+    // (138 MB) 3.00 / 2.72, 2600 4.34 / 4.49; of four: 700 (147 MB) 1.36 / 1.32,
+    // 1354 (276 MB) 4.59 / 4.68; of eight: 300 1.13 / 1.17.  FP32, two: 300 1.20 /
+    // 1.07, 2600 (123 MB) 5.98 / 5.61; four: 1354 5.72 / 5.42, 2600 8.08 / 8.80;
+    // eight: 700 (147 MB) 3.24 / 3.12, 1000 3.74 / 3.90; sixteen: 300 2.44 / 2.46.
+    // And rows where a row is long: the steps of one row are a chain that the
+    // levels do not pipeline (FP64 slices of two, a hub of 400 leaves: 0.98 /
+    // 1.40, of 200: 1.06 / 1.12).
+    if (S.max_row_blocks > 128 || slice * tsz >= 64) return true;
+    return (size_t)h.n_cu * slice * S.nnzb() * 4 * tsz >= 150u * 1000 * 1000;
+  }
+  // One scenario: as tasks, which need many wavefronts to overlap the levels.
+  // From twelve on FP64 always (x250: 300 buses 0.285 / 0.312, 1354 0.985 / 1.00,
+  // 4000 2.08 / 2.53), FP32 on the larger grids (x250: 1354 1.63 / 1.56, 2800
+  // 2.37 / 2.34, 3400 2.44 / 2.50, 9241 8.75 / 9.45).  A compute unit holds two
+  // or more of the narrower workgroups by levels, fewer with the row buffers:
+  // eight wavefronts, FP64 x250: 1354 1.17 / 1.06, 2600 1.47 / 1.47, 4000 2.35 /
+  // 2.64, FP32: 4000 3.53 / 3.45, 9241 10.7 / 11.1; four, FP64: 1354 1.77 / 1.38,
+  // 9241 x250 12.4 / 13.4, x500 24.8 / 21.1; one, 9241 x250: 38.2 / 35.6.
+  if (h.threads >= 768) return !h.fp32 || S.nb >= 3072;
+  if (h.threads >= 512) return S.nb >= (h.fp32 ? 4096 : 2560);
+  return h.threads >= 256 && S.nb >= 4096 && h.batch <= h.n_cu;
+}
+
 }  // namespace
 
 int plan_hbm(const Symbolic& S, const HbmShape& h, HbmPlan& p, std::string& err) {
@@ -118,12 +151,6 @@ int plan_hbm(const Symbolic& S, const HbmShape& h, HbmPlan& p, std::string& err)
   // although two by levels would be faster (x600: 10.4 against 13.0 ms).
   p = HbmPlan{};
   while (p.slice < kMaxSlice && h.batch / (2 * p.slice) >= h.n_cu) p.slice *= 2;
-  // Slices of one scenario with FP32 factors factor by levels in place on the
-  // smaller grids: there a levelled pass costs little more than its barrier
-  // (1354 buses x250, mixed: 1.55 ms by levels, 1.65 by rows; FP64 0.97 both;
-  // 300 buses x250, FP64: 0.36 and 0.34; 9241 buses x256, mixed: 9.4 and 8.8,
-  // FP64 9.6 and 6.5).
-  const bool by_levels = h.fp32 && S.nb < 4096;
   while (p.slice > 1 && fixed_bytes(S) + tail_copy_bytes(S, p.slice, h.fp32) + 4 * kMinChunkInts > h.max_lds) p.slice /= 2;
   const int width = p.slice;
   auto rows_fit = [&](int slice) {
@@ -136,8 +163,9 @@ int plan_hbm(const Symbolic& S, const HbmShape& h, HbmPlan& p, std::string& err)
       if (plan_slice(S, h, true, false, waves /= 2, p, err) == 0) return true;
     return false;
   };
-  if (width > 1 ? rows_fit(width) || (width > 2 && rows_fit(width / 2)) : !by_levels && rows_fit(1)) return 0;
-  for (p.slice = width > 2 || h.fp32 ? width : 1; p.slice >= 1; p.slice /= 2)
+  const bool rows = prefer_rows(S, h, width);
+  if (rows && (rows_fit(width) || (width > 2 && rows_fit(width / 2)))) return 0;
+  for (p.slice = rows && width == 2 && !h.fp32 ? 1 : width; p.slice >= 1; p.slice /= 2)
     if (plan_slice(S, h, false, true, 0, p, err) == 0) return 0;
   return PF_EINVAL;
 }

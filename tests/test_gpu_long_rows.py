@@ -1,12 +1,14 @@
-"""Networks with long rows on the HBM-resident paths, against the dense oracle:
-a row whose task record and buffer take the share of several wavefronts, so that
-only some of them take tasks, with wide and narrow workgroups."""
+"""The HBM-resident paths against the dense oracle where other tests do not take
+them: long rows (a task record and a buffer beyond a wavefront's share, a row
+that fits no row chunk), narrow slices row by row, tasks of narrow workgroups."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
 from test_gpu_rows import _check
 from test_host_plan import hubs
-from gen.grids import Scenarios
+from gen.grids import GridSpec, Scenarios, make_network, make_scenarios
 
 pytestmark = pytest.mark.gpu
 
@@ -16,6 +18,14 @@ def _scenarios(net, batch, seed=3):
     pq = np.asarray(net.bus_type) == 0
     pd = np.where(pq, rng.uniform(1e-5, 2e-5, (batch, net.n_bus)), 0.0)
     return Scenarios(pd, 0.3 * pd, np.zeros_like(pd), np.ones_like(pd))
+
+
+def _path(net, batch, precision, **kw):
+    from paper_2606_07099_amd import PFTemplate
+    tpl = PFTemplate.from_network(net, batch, precision=precision, **kw)
+    path = tpl.info()["factor_path"]
+    tpl.close()
+    return path
 
 
 @pytest.mark.parametrize("leaves", [150, 200, 235])
@@ -45,3 +55,28 @@ def test_wide_slices_by_levels_match_the_oracle(batch, slice_width, device):
     net = hubs(20, 2000, 1)
     sc = _scenarios(net, batch)
     _check(net, sc, 1e-9, "fp64", device, (batch - 1,), slice_width)
+
+
+def _grid(n, batch):
+    """A grid of n buses at a load that the flat start converges from."""
+    spec = GridSpec("sized", 100, n, round(0.3 * n), round(1.4 * n), 1, 0.10, 1e-8, load_factor=0.05,
+                    z_scale=min(1.0, (118 / n) ** 0.5))
+    net = make_network(spec, 1)
+    net = replace(net, vset=1.0 + 0.3 * (net.vset - 1.0))
+    return net, make_scenarios(net, spec, batch, 1)
+
+
+@pytest.mark.parametrize("n,batch,precision,slice_width", [(1000, 1030, "fp64", 4), (1700, 520, "fp64", 2),
+                                                           (1700, 1030, "mixed", 4), (3200, 520, "mixed", 2)])
+def test_narrow_slices_row_by_row_match_the_oracle(n, batch, precision, slice_width, device):
+    net, sc = _grid(n, batch)
+    assert _path(net, batch, precision) == "rows"
+    _check(net, sc, 1e-8, precision, device, (batch - 1,), slice_width)
+
+
+# few wavefronts, all of which wait for each other's rows
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_tasks_of_a_narrow_workgroup_match_the_oracle(precision, device):
+    net, sc = _grid(4200, 3)
+    assert _path(net, 3, precision, block_threads=256) == "tasks"
+    _check(net, sc, 1e-8, precision, device, (2,), 1, block_threads=256)

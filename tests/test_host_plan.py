@@ -97,6 +97,27 @@ def test_narrow_workgroups_take_the_lds_they_use(checker, tmp_path, n, precision
         assert 3 * p["lds"] <= 160 * 1024
 
 
+# either side of the lines between rows and levels
+@pytest.mark.parametrize("n,precision,batch,threads,path", [
+    (300, "fp64", 600, 1024, "levels"), (1354, "fp64", 600, 1024, "levels"), (2600, "fp64", 600, 1024, "rows"),
+    (700, "fp64", 1100, 1024, "levels"), (1354, "fp64", 1100, 1024, "rows"), (300, "fp64", 2100, 1024, "rows"),
+    (300, "mixed", 600, 1024, "levels"), (2600, "mixed", 600, 1024, "levels"), (1354, "mixed", 1100, 1024, "levels"),
+    (2600, "mixed", 1100, 1024, "rows"), (300, "mixed", 2100, 1024, "levels"), (1100, "mixed", 2100, 1024, "rows"),
+    (300, "mixed", 4200, 1024, "rows"), (300, "fp64", 250, 768, "tasks"), (2800, "mixed", 250, 1024, "levels"),
+    (3400, "mixed", 250, 1024, "tasks"), (1354, "fp64", 400, 512, "levels"), (4000, "fp64", 400, 512, "tasks"),
+    (4000, "mixed", 250, 512, "levels"), (300, "fp64", 400, 256, "levels"), (5000, "fp64", 250, 256, "tasks"),
+    (5000, "fp64", 400, 256, "levels"), (5000, "fp64", 250, 192, "levels")])
+def test_rows_and_levels_where_each_is_the_faster(checker, tmp_path, n, precision, batch, threads, path):
+    p = plan(checker, write(tmp_path / "net.txt", grid(n)), precision, batch, threads)
+    assert p["path"] == path and p["slice"] == {2: 2, 4: 4, 8: 8, 16: 16}.get(batch // 256, 1)
+
+
+def test_long_rows_of_wide_slices_go_row_by_row(checker, tmp_path):
+    path = write(tmp_path / "net.txt", hubs(400, 150))
+    assert plan(checker, path, "fp64", 600)["path"] == "rows"
+    assert plan(checker, write(tmp_path / "net.txt", hubs(400, 100)), "fp64", 600)["path"] == "levels"
+
+
 @pytest.mark.parametrize("precision,batch,slice_width",
                          [("mixed", 600, 2), *((p, *x) for p in ("fp64", "mixed")
                                                for x in ((1100, 4), (2100, 8), (4200, 16)))])
