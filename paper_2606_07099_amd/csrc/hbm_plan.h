@@ -28,8 +28,11 @@ constexpr int32_t kChunkInts = 12288;
 constexpr int32_t tail_max_rows(bool fp32) { return fp32 ? 32 : 16; }
 // And an FP64 tail takes in levels of at most four rows: a row costs the tail
 // 0.7 us per factorisation, a level outside it 2.6 us per update (factor and
-// backward pass), which the tail's wavefront alone no longer beats.  With FP32
-// factors a level also costs the refinement's four solves, a tail row less.
+// backward pass), which the tail's wavefront alone no longer beats.  So it is in
+// HBM-resident templates, though only networks of a few buses have such levels at
+// the top (14 buses, block_threads 256, x600: 98 us with the limit, 105 without,
+// x4096: 214 and 306; 150 buses x4096: 0.83 and 0.89 ms).  With FP32 factors a
+// level also costs the refinement's four solves, a tail row less.
 constexpr int32_t tail_max_level(bool fp32) { return fp32 ? tail_max_rows(true) : 4; }
 
 // How a template factors: by levels in place, or row by row (one scenario per
