@@ -9,7 +9,7 @@ import subprocess
 import numpy as np
 import pytest
 
-from gen.grids import GridSpec, Network, make_network
+from gen.grids import GridSpec, Network, SPECS, make_network
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_07099_amd", "csrc")
@@ -95,6 +95,14 @@ def test_narrow_workgroups_take_the_lds_they_use(checker, tmp_path, n, precision
     p = plan(checker, write(tmp_path / "net.txt", grid(n)), precision, batch, threads)
     if threads == 64 and n <= 300 and p["slice"] <= 2:   # several of them fit a compute unit
         assert 3 * p["lds"] <= 160 * 1024
+
+
+@pytest.mark.parametrize("name,precision,batch,path", [
+    ("c1", "fp64", 37, "tasks"), ("c2", "fp64", 37, "tasks"), ("c4", "fp64", 256, "tasks"),
+    ("c4", "mixed", 256, "tasks"), ("c3", "fp64", 2048, "rows"), ("c2", "fp64", 4096, "rows"),
+    ("c2", "mixed", 4096, "rows"), ("c4", "fp64", 1100, "rows")])
+def test_named_grids_replay_their_schedules(checker, tmp_path, name, precision, batch, path):
+    assert plan(checker, write(tmp_path / "net.txt", make_network(SPECS[name])), precision, batch)["path"] == path
 
 
 # either side of the lines between rows and levels
