@@ -96,25 +96,56 @@ int plan_slice(const Symbolic& S, const HbmShape& h, bool rows, bool want_y, int
   return 0;
 }
 
+// the elimination steps that follow one another: row by row, the most of a row
+// in each level; by levels, the most that a row takes in each of them
+struct Chains { int64_t rows = 0, levels = 0; };
+Chains step_chains(const Symbolic& S) {
+  Chains c;
+  auto steps = [&](int32_t a) { return (a < S.tail_base ? S.diag[a] : S.tail_split[a - S.tail_base]) - S.rp[a]; };
+  for (int32_t h = 0; h < S.n_fs_levels; ++h) {
+    int32_t most = 0;
+    for (int32_t q = S.lev_l_ptr[h]; q < S.lev_l_ptr[h + 1]; ++q) most = std::max(most, steps(S.lev_l_rows[q]));
+    c.rows += most;
+  }
+  int32_t tail = 0;
+  for (int32_t a = S.tail_base; a < S.nb; ++a) tail = std::max(tail, steps(a));
+  c.rows += tail;
+  for (int32_t h = 0; h < S.n_task_levels; ++h) {
+    int32_t most = 0;
+    for (int32_t i = S.task_ptr[h]; i < S.task_ptr[h + 1]; ++i)
+      most = std::max(most, S.task4[4 * (size_t)i + 2] - S.task4[4 * (size_t)i + 1]);
+    c.levels += most;
+  }
+  return c;
+}
+
 // Whether slices of this many scenarios rather factor row by row than by levels.
 // The rows move fewer bytes, the levels have more lanes at work and wait less on
-// one row after the other (solves below in ms, by rows / by levels, with 1024
+// one step after the other (solves below in ms, by rows / by levels, with 1024
 // threads and the batches that give this width).
 bool prefer_rows(const Symbolic& S, const HbmShape& h, int slice) {
   const size_t tsz = h.fp32 ? 4 : 8;
   if (slice > 1) {
-    // Levels while the factors of one slice per compute unit stay well inside
-    // the 256 MB Infinity Cache, and one value of all scenarios of a block is
-    // short of a 64-byte run.  FP64 slices of two: 300 buses 0.78 / 0.68, 1354
-    // (138 MB) 3.00 / 2.72, 2600 4.34 / 4.49; of four: 700 (147 MB) 1.36 / 1.32,
-    // 1354 (276 MB) 4.59 / 4.68; of eight: 300 1.13 / 1.17.  FP32, two: 300 1.20 /
-    // 1.07, 2600 (123 MB) 5.98 / 5.61; four: 1354 5.72 / 5.42, 2600 8.08 / 8.80;
-    // eight: 700 (147 MB) 3.24 / 3.12, 1000 3.74 / 3.90; sixteen: 300 2.44 / 2.46.
-    // And rows where a row is long: the steps of one row are a chain that the
-    // levels do not pipeline (FP64 slices of two, a hub of 400 leaves: 0.98 /
-    // 1.40, of 200: 1.06 / 1.12).
-    if (S.max_row_blocks > 128 || slice * tsz >= 64) return true;
-    return (size_t)h.n_cu * slice * S.nnzb() * 4 * tsz >= 150u * 1000 * 1000;
+    // Rows where one value of all scenarios of a block is a run of 64 bytes or
+    // more (FP64, eight: 300 buses 1.13 / 1.17, 1354 6.29 / 8.03; FP32, sixteen:
+    // 300 2.44 / 2.46) ...
+    if (slice * tsz >= 64) return true;
+    // ... or where a few long rows make the levels as serial (FP64, two: a hub of
+    // 400 leaves 0.98 / 1.40, two of 200 1.06 / 1.12) ...
+    const Chains c = step_chains(S);
+    const double serial = double(c.rows) - 2.0 * c.levels;   // a step of a level takes about two of a row
+    if (8 * serial <= c.rows) return true;
+    // ... else where the factors of one slice per compute unit leave the 256 MB
+    // Infinity Cache (with the rest of the state, from about 175 MB on), and are
+    // large against the rows' chain of steps.  FP64, two: 1354 buses (138 MB) 3.00 /
+    // 2.72, 2600 (0.63 MB per step) 4.33 / 4.49, 1200 of three branches each
+    // (0.16) 7.75 / 6.42; four: 700 (147 MB) 1.36 / 1.32, 1354 (1.2) 4.59 / 4.68,
+    // the 1200 (0.32) 10.4 / 10.1, 2000 of two branches (0.51) 8.66 / 9.00.  FP32,
+    // four: 1354 (138 MB) 5.72 / 5.42, 2600 (1.1) 8.08 / 8.80, the 2000 (0.39) 9.46 /
+    // 9.30; eight: 700 (147 MB) 3.24 / 3.12, 1000 (183 MB) 3.74 / 3.90, the 1200
+    // (0.51) 13.6 / 13.9.
+    const double mb = 1e-6 * h.n_cu * slice * S.nnzb() * 4 * tsz;
+    return mb >= 175 && mb >= 0.5 * serial;
   }
   // One scenario: as tasks, which need many wavefronts to overlap the levels.
   // From twelve on FP64 always (x250: 300 buses 0.285 / 0.312, 1354 0.985 / 1.00,

@@ -66,12 +66,34 @@ def _grid(n, batch):
     return net, make_scenarios(net, spec, batch, 1)
 
 
-@pytest.mark.parametrize("n,batch,precision,slice_width", [(1000, 1030, "fp64", 4), (1700, 520, "fp64", 2),
-                                                           (1700, 1030, "mixed", 4), (3200, 520, "mixed", 2)])
+@pytest.mark.parametrize("n,batch,precision,slice_width", [(1200, 1030, "fp64", 4), (2300, 520, "fp64", 2),
+                                                           (2300, 1030, "mixed", 4)])
 def test_narrow_slices_row_by_row_match_the_oracle(n, batch, precision, slice_width, device):
     net, sc = _grid(n, batch)
     assert _path(net, batch, precision) == "rows"
     _check(net, sc, 1e-8, precision, device, (batch - 1,), slice_width)
+
+
+def test_mixed_rows_of_two_match_fp64(device):
+    """Only the largest grid takes them: too large for the dense oracle."""
+    import torch
+    from oracle.adjoint import loss_grad
+    from gpu_helpers import make_gpu_case
+    out = {}
+    for precision in ("fp64", "mixed"):
+        spec, net, sc, tpl, d, tol = make_gpu_case("c4", device, batch=513, precision=precision)
+        info = tpl.info()
+        assert info["factor_path"] == "rows" and info["slice_width"] == 2
+        vm, va, _, status, _ = tpl.solve(*(d[k] for k in ("pd", "qd", "pg", "vset")))
+        if precision == "fp64":
+            upstream = [torch.as_tensor(x, device=device) for x in loss_grad(vm.cpu().numpy(), va.cpu().numpy())]
+        g = tpl.adjoint(*upstream)
+        torch.cuda.synchronize()
+        assert int((status != 0).sum()) == 0
+        out[precision] = [vm, va, *g]
+        tpl.close()
+    for i, (a, b) in enumerate(zip(out["fp64"], out["mixed"])):
+        assert float((a - b).abs().max()) <= (1e-8 if i < 2 else 1e-6 * float(a.abs().max()))
 
 
 # few wavefronts, all of which wait for each other's rows

@@ -27,7 +27,7 @@ def _with_dead_bus(net):
 @pytest.mark.parametrize("n,batch,precision,path,slice_width", [
     (300, 5, "fp64", "tasks", 1), (3200, 5, "mixed", "tasks", 1), (300, 5, "mixed", "levels", 1),
     (300, 513, "fp64", "levels", 2), (300, 1027, "mixed", "levels", 4), (300, 2049, "mixed", "levels", 8),
-    (1700, 513, "fp64", "rows", 2), (1000, 1027, "fp64", "rows", 4), (300, 2049, "fp64", "rows", 8),
+    (2300, 513, "fp64", "rows", 2), (1000, 1027, "fp64", "rows", 4), (300, 2049, "fp64", "rows", 8),
     (300, 4099, "mixed", "rows", 16)])
 def test_a_zero_pivot_is_reported(n, batch, precision, path, slice_width, device):
     import torch

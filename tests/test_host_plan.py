@@ -29,9 +29,9 @@ def checker(tmp_path_factory):
     return out
 
 
-def grid(n, seed=1):
-    return make_network(GridSpec("sized", 100, n, round(0.3 * n), round(1.4 * n), 1, 0.10, 1e-8, load_factor=0.05),
-                        seed)
+def grid(n, seed=1, branches=1.4):
+    return make_network(GridSpec("sized", 100, n, round(0.3 * n), round(branches * n), 1, 0.10, 1e-8,
+                                 load_factor=0.05), seed)
 
 
 def hubs(n, leaves, count=2):
@@ -123,7 +123,15 @@ def test_rows_and_levels_where_each_is_the_faster(checker, tmp_path, n, precisio
 def test_long_rows_of_wide_slices_go_row_by_row(checker, tmp_path):
     path = write(tmp_path / "net.txt", hubs(400, 150))
     assert plan(checker, path, "fp64", 600)["path"] == "rows"
-    assert plan(checker, write(tmp_path / "net.txt", hubs(400, 100)), "fp64", 600)["path"] == "levels"
+    assert plan(checker, write(tmp_path / "net.txt", hubs(400, 20)), "fp64", 600)["path"] == "levels"
+
+
+def test_meshed_networks_of_few_scenarios_go_by_levels(checker, tmp_path):
+    """Three branches per bus: the chain of a row's steps outweighs the bytes."""
+    path = write(tmp_path / "net.txt", grid(1200, branches=3.0))
+    assert plan(checker, path, "fp64", 600)["path"] == "levels"
+    assert plan(checker, path, "fp64", 1100)["path"] == "levels"
+    assert plan(checker, path, "fp64", 2100)["path"] == "rows"
 
 
 @pytest.mark.parametrize("precision,batch,slice_width",
