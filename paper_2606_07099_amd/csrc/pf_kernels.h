@@ -87,7 +87,7 @@ struct Dims {
   int tail_t, tail_base;          // dense tail rows [tail_base, tail_base + tail_t)
   int nch_f, nch_fs, nch_bs;      // metadata chunks of the factor, forward and backward levels
   int nch_r;                      // metadata chunks of the row-by-row factorisation
-  int n_flow, flow_levels;        // its wavefront tasks and their levels (0: chunks only)
+  int n_flow, flow_levels;        // its wavefront tasks and their levels (0: chunks, or by levels in place)
   int flow_waves;                 // wavefronts that take tasks
   int flow_meta;                  // words of a wavefront's task record area
   int flow_buf;                   // row buffer of a wavefront, in blocks of one scenario

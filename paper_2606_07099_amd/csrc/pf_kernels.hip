@@ -18,9 +18,8 @@
 //    workspace, interleaved the same way, the symbolic arrays are read from the
 //    shared image (L2).  Up-looking LU, each row formed and eliminated in LDS:
 //    by levels with a barrier each (several scenarios), or as wavefront tasks
-//    that wait for each other's rows (one scenario).  Slices of one scenario
-//    whose rows do not fit, or with FP32 factors on smaller grids, factor by
-//    levels in place.
+//    that wait for each other's rows (one scenario); or right-looking by levels
+//    in place, where that is the faster or the rows do not fit.
 #include "pf_kernels.h"
 
 #include <hip/hip_runtime.h>
