@@ -52,15 +52,15 @@ KERNEL_SOURCES = ("paper_2606_07099_amd/csrc/pf_kernels.hip", "paper_2606_07099_
 # the kernel sources they were taken on; a changed kernel reports null.
 # Sources: profiles/*_hbm_counters.md
 MEASURED_TRAFFIC = {
-    "e7090cbcd346056ea15b8c988819d2a38513d591362b3b0d3f41dd58bcc91f96": {
-        "c1/mixed": 6967990,
-        "c1/fp64": 6901440,
-        "c2/mixed": 35279100000,
-        "c2/fp64": 27374300000,
-        "c3/mixed": 2524166000,
-        "c3/fp64": 2008802000,
-        "c4/mixed": 31073140000,
-        "c4/fp64": 29438650000,
+    "afd1688a7b58bd55d689024f6ac21c961679901ae2e6ed2fc2d3458ace18a060": {
+        "c1/mixed": 6966980,
+        "c1/fp64": 6895300,
+        "c2/mixed": 35234740000,
+        "c2/fp64": 27367870000,
+        "c3/mixed": 3020140000,
+        "c3/fp64": 2008305000,
+        "c4/mixed": 31072080000,
+        "c4/fp64": 29410110000,
     },
 }
 
