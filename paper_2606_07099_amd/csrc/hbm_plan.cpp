@@ -126,6 +126,11 @@ Chains step_chains(const Symbolic& S) {
 bool prefer_rows(const Symbolic& S, const HbmShape& h, int slice) {
   const size_t tsz = h.fp32 ? 4 : 8;
   if (slice > 1) {
+    // Networks of a few buses, which only block_threads brings here, by levels:
+    // nearly all their rows are in the tail (with the adjoint, FP32: 14 buses x600,
+    // 256 threads 0.244 / 0.226, x4096, 1024 threads 0.301 / 0.286; 30 x4096 0.387 /
+    // 0.372).
+    if (S.nb < 48) return false;
     // Rows where one value of all scenarios of a block is a run of 64 bytes or
     // more (FP64, eight: 300 buses 1.13 / 1.17, 1354 6.29 / 8.03; FP32, sixteen:
     // 300 2.44 / 2.46) ...
@@ -134,7 +139,7 @@ bool prefer_rows(const Symbolic& S, const HbmShape& h, int slice) {
     // 400 leaves 0.98 / 1.40, two of 200 1.06 / 1.12) ...
     const Chains c = step_chains(S);
     const double serial = double(c.rows) - 2.0 * c.levels;   // a step of a level takes about two of a row
-    if (8 * serial <= c.rows) return true;
+    if (c.rows >= 128 && 8 * serial <= c.rows) return true;
     // ... else where the factors of one slice per compute unit leave the 256 MB
     // Infinity Cache (with the rest of the state, from about 175 MB on), and are
     // large against the rows' chain of steps.  FP64, two: 1354 buses (138 MB) 3.00 /

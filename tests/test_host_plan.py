@@ -114,6 +114,7 @@ def test_named_grids_replay_their_schedules(checker, tmp_path, name, precision, 
     (300, "mixed", 4200, 1024, "rows"), (300, "fp64", 250, 768, "tasks"), (2800, "mixed", 250, 1024, "levels"),
     (3400, "mixed", 250, 1024, "tasks"), (1354, "fp64", 400, 512, "levels"), (4000, "fp64", 400, 512, "tasks"),
     (4000, "mixed", 250, 512, "levels"), (300, "fp64", 400, 256, "levels"), (5000, "fp64", 250, 256, "tasks"),
+    (30, "fp64", 4200, 256, "levels"), (30, "mixed", 600, 64, "levels"), (57, "fp64", 4200, 256, "rows"),
     (5000, "fp64", 400, 256, "levels"), (5000, "fp64", 250, 192, "levels")])
 def test_rows_and_levels_where_each_is_the_faster(checker, tmp_path, n, precision, batch, threads, path):
     p = plan(checker, write(tmp_path / "net.txt", grid(n)), precision, batch, threads)
